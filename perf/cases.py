@@ -1,0 +1,843 @@
+"""What a user has this framework do, as cases that can be timed.
+
+listed() and draw() give cases, prepare() what a program holds before the
+call (initial condition, run context, server), run() one pass through the
+public entry points, work() the bytes and operations of a pass, exact() the
+same outputs from plain float64 torch code.
+
+The kinds of case:
+
+  poisson   the force of a given density (poisson_static): the smallest call;
+  run       a whole run segment of VlasovRun: new initial condition, the
+            leapfrog steps with their resamplings, f (in FP64 the density
+            too) at the end (isolated or periodic x, fixed or variable step,
+            fixed or adaptive resampling, both precisions);
+  snapshot  what a run writes out at an output time: f by both schemes, the
+            density and the diagnostics of section 3.2;
+  serve     a batch of independent runs through the Server;
+  run4      a run segment of the 4D engine;
+  snapshot4 the 4D engine's output time.
+"""
+import math
+
+import numpy as np
+import torch
+
+import paper_1705_03750_amd as vp
+from paper_1705_03750_amd import vp4
+
+BOX = (-1.0, 1.0, -1.0, 1.0)             # self-gravitating halos
+RING = (0.0, 10.0 * math.pi, -8.0, 8.0)  # two-stream plasma, x periodic
+
+
+def listed():
+    return [
+        # the force of one density of the 256-site run: latency alone
+        dict(name="poisson_256", kind="poisson", nx=256, bc=0),
+        # a 256^2 run over a resampling and some steps after it
+        dict(name="run_256_fp64", kind="run", nx=256, nv=256, sx=4, sv=4,
+             steps=25, n_s=20, dt=1e-3, precision="fp64", bc=0, c_dyn=0.0,
+             emap_max=0.0, emap_every=0),
+        # the benchmark's 2048^2 halos over a resampling and some steps more
+        dict(name="run_2048_mixed", kind="run", nx=2048, nv=2048, sx=8, sv=8,
+             steps=50, n_s=40, dt=5e-4, precision="mixed", bc=0, c_dyn=0.0,
+             emap_max=0.0, emap_every=0),
+        # ragged grid, variable step, resampling decided by E_map
+        dict(name="adaptive_1020x1004_fp64", kind="run", nx=1020, nv=1004,
+             sx=4, sv=4, steps=40, n_s=0, dt=1e-3, precision="fp64", bc=0,
+             c_dyn=8e-4, emap_max=2e-4, emap_every=10),
+        # the two-stream plasma on a ring, the same way
+        dict(name="ring_2048_mixed", kind="run", nx=2048, nv=2048, sx=8, sv=8,
+             steps=50, n_s=40, dt=0.05, precision="mixed", bc=1, c_dyn=0.0,
+             emap_max=0.0, emap_every=0),
+        # the benchmark's large grids
+        dict(name="run_8192_fp64", kind="run", nx=8192, nv=8192, sx=8, sv=8,
+             steps=50, n_s=40, dt=2.5e-4, precision="fp64", bc=0, c_dyn=0.0,
+             emap_max=0.0, emap_every=0),
+        dict(name="run_16384_mixed", kind="run", nx=16384, nv=16384, sx=16,
+             sv=16, steps=20, n_s=16, dt=1.25e-4, precision="mixed", bc=0,
+             c_dyn=0.0, emap_max=0.0, emap_every=0),
+        # an output time of the 2048^2 run in FP64
+        dict(name="snapshot_2048_fp64", kind="snapshot", nx=2048, nv=2048,
+             sx=8, sv=8, steps=30, n_s=0, dt=5e-4, precision="fp64", bc=0),
+        # the serving mix: grids of 256 to 2048 sites, strides 4 and 8
+        dict(name="serve_24_mixed", kind="serve", count=24, n_max=2048,
+             steps_min=40, steps_max=160, precision="mixed"),
+        # the 4D plasma: a test-sized grid, the benchmark's, an output time
+        dict(name="run4_16_fp64", kind="run4", ns=16, nv=16, ss=4, sv=4,
+             steps=10, n_s=4, dt=0.1, precision="fp64"),
+        dict(name="run4_64_mixed", kind="run4", ns=64, nv=64, ss=4, sv=4,
+             steps=10, n_s=8, dt=0.1, precision="mixed"),
+        dict(name="snapshot4_32x24_fp64", kind="snapshot4", ns=32, nv=24,
+             ss=4, sv=4, steps=4, n_s=0, dt=0.1, precision="fp64"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _draw_grid(rng, ring):
+    """Sites and strides of a 2D grid, 64 to 4096 sites per axis."""
+    sx, sv = rng.choice((4, 4, 8, 8, 16)), rng.choice((4, 8, 8, 16))
+    nx = sx * max(2, _log_int(rng, 64, 4096) // sx)
+    nv = sv * max(2, _log_int(rng, 64, 4096) // sv)
+    return (8 * ((nx + 7) // 8) if ring and sx < 8 else nx), nv, sx, sv
+
+
+def draw(rng):
+    kind = rng.choice(("poisson", "run", "run", "run", "run", "snapshot",
+                       "serve", "run4", "run4", "snapshot4"))
+    prec = rng.choice(("fp64", "mixed"))
+    if kind == "poisson":
+        return dict(kind=kind, nx=8 * _log_int(rng, 8, 2048),
+                    bc=rng.choice((0, 0, 1)))
+    if kind in ("run", "snapshot"):
+        bc = rng.choice((0, 0, 1))
+        nx, nv, sx, sv = _draw_grid(rng, bc)
+        dt = rng.uniform(0.02, 0.06) if bc else \
+            min(1e-3, rng.uniform(0.5, 1.5) / max(nx, nv))
+        steps = rng.randint(4, 40)
+        case = dict(kind=kind, nx=nx, nv=nv, sx=sx, sv=sv, steps=steps,
+                    n_s=rng.randint(5, 40) if kind == "run" else 0, dt=dt,
+                    precision=prec, bc=bc)
+        if kind == "run":
+            vary = rng.random() < 0.25
+            case.update(c_dyn=(0.6 if bc else 0.8) * dt if vary else 0.0,
+                        emap_max=0.0, emap_every=0)
+        return case
+    if kind == "serve":
+        lo = rng.randint(20, 60)
+        return dict(kind=kind, count=rng.randint(4, 24),
+                    n_max=rng.choice((512, 1024, 2048)), steps_min=lo,
+                    steps_max=2 * lo, precision=prec)
+    ss, sv = rng.choice((4, 4, 8)), 4
+    return dict(kind=kind, ns=ss * rng.randint(2, 40 // ss + 1) if ss == 4 else
+                8 * rng.randint(2, 4), nv=4 * rng.randint(3, 10), ss=ss, sv=sv,
+                steps=rng.randint(2, 10),
+                n_s=rng.randint(2, 10) if kind == "run4" else 0,
+                dt=rng.uniform(0.05, 0.15), precision=prec)
+
+
+# ------------------------------------------------------------------ inputs
+
+def _device():
+    return torch.device("cuda:0" if torch.cuda.is_available() else "cpu")
+
+
+def _sites(n, lo, hi):
+    d = (hi - lo) / n
+    return lo + (torch.arange(n, dtype=torch.float64, device=_device()) + 0.5) * d
+
+
+def _halos(nx, nv, rng):
+    """Seeded sum of 1 to 8 Gaussian halos of total mass 1, edge ring zero."""
+    k = int(rng.integers(1, 9))
+    xc, vc = rng.uniform(-0.5, 0.5, k), rng.uniform(-0.3, 0.3, k)
+    sx, sv = rng.uniform(0.05, 0.15, k), rng.uniform(0.05, 0.15, k)
+    w = rng.dirichlet(np.ones(k)) / (2.0 * math.pi * sx * sv)
+    x, v = _sites(nx, -1.0, 1.0), _sites(nv, -1.0, 1.0)
+    f = torch.zeros((nv, nx), dtype=torch.float64, device=x.device)
+    for a in range(k):
+        f.addr_(torch.exp(-0.5 * ((v - vc[a]) / sv[a]) ** 2) * w[a],
+                torch.exp(-0.5 * ((x - xc[a]) / sx[a]) ** 2))
+    f[0] = f[-1] = 0.0
+    f[:, 0] = f[:, -1] = 0.0
+    f[f < 1e-30 * f.max()] = 0.0
+    return f * (nx * nv / 4.0 / f.sum())
+
+
+def _beams(nx, nv, rng):
+    """Two Maxwellian beams with a seeded density perturbation, mean 1."""
+    x, v = _sites(nx, RING[0], RING[1]), _sites(nv, RING[2], RING[3])
+    v0, al, ph = rng.uniform(2.0, 2.6), rng.uniform(0.005, 0.02), rng.uniform(0, 6)
+    beams = 0.5 * (torch.exp(-0.5 * (v - v0) ** 2) + torch.exp(-0.5 * (v + v0) ** 2))
+    f = torch.outer(beams / math.sqrt(2.0 * math.pi),
+                    1.0 + al * torch.cos(0.2 * x + ph))
+    f[0] = f[-1] = 0.0
+    return f
+
+
+def _f0(case, seed):
+    rng = np.random.default_rng(seed)
+    make = _beams if case["bc"] else _halos
+    return make(case["nx"], case["nv"], rng)
+
+
+def _params(case):
+    box = RING if case["bc"] else BOX
+    p = {k: case[k] for k in ("nx", "nv", "sx", "sv", "n_s", "dt", "bc")}
+    p.update(zip(("x_min", "x_max", "v_min", "v_max"), box))
+    p.update({k: case[k] for k in ("c_dyn", "emap_max", "emap_every")
+              if k in case})
+    p["G"] = -0.5 if case["bc"] else 1.0
+    return p
+
+
+def _rho(case, seed):
+    """A density with the ripples of a projected halo sum (mean 1 on a ring)."""
+    rng = np.random.default_rng(seed)
+    f = _beams(case["nx"], 64, rng) if case["bc"] else _halos(case["nx"], 64, rng)
+    noise = torch.as_tensor(rng.standard_normal(case["nx"]), device=f.device)
+    return f.mean(0) * (1.0 + 1e-3 * noise) * (16.0 if case["bc"] else 2.0)
+
+
+def _poisson_kw(case):
+    p = _params(dict(case, nv=8, sx=4, sv=4, n_s=0, dt=1e-3))
+    del p["nx"]
+    return p
+
+
+L4, V4 = 4.0 * math.pi, 6.0
+
+
+def _f04(case, seed):
+    """Maxwellian plasma with the four lowest Fourier modes perturbed."""
+    rng = np.random.default_rng(seed)
+    x, u = _sites(case["ns"], 0.0, L4), _sites(case["nv"], -V4, V4)
+    pert = torch.ones((case["ns"],) * 2, dtype=torch.float64, device=x.device)
+    for mx, my in ((1, 0), (0, 1), (1, 1), (1, -1)):
+        pert += 0.05 * rng.uniform(0.5, 1.0) * torch.cos(
+            2.0 * math.pi * (mx * x[None, :] + my * x[:, None]) / L4
+            + rng.uniform(0, 2 * math.pi))
+    g = torch.exp(-0.5 * u ** 2) / math.sqrt(2.0 * math.pi)
+    g[0] = g[-1] = 0.0
+    return (g[:, None, None, None] * g[None, :, None, None]) * pert
+
+
+def _params4(case):
+    p = {k: case[k] for k in ("ns", "nv", "ss", "sv", "n_s", "dt")}
+    return dict(p, L=L4, vmax=V4, G=-0.5)
+
+
+def _requests(case, seed):
+    """(case of each request, its seed): N and stride uniform over the mix,
+    the same grids for every seed."""
+    rng = np.random.default_rng(case["count"])
+    sizes = [n for n in (256, 512, 1024, 2048) if n <= case["n_max"]]
+    out = []
+    for r in range(case["count"]):
+        n, s = int(rng.choice(sizes)), int(rng.choice((4, 8)))
+        steps = int(rng.integers(case["steps_min"], case["steps_max"] + 1))
+        out.append((dict(nx=n, nv=n, sx=s, sv=s, steps=steps,
+                         n_s=int(rng.integers(25, 51)), dt=5e-4, bc=0),
+                    1000 * seed + r))
+    return out
+
+
+def prepare(case, seed):
+    kind = case["kind"]
+    if kind == "poisson":
+        return dict(kind=kind, rho=_rho(case, seed), kw=_poisson_kw(case))
+    if kind == "serve":
+        reqs = []
+        dt = torch.float32 if case["precision"] == "mixed" else torch.float64
+        need = 0
+        for c, s in _requests(case, seed):
+            p = dict(_params(c), precision=case["precision"])
+            need += vp.footprint(**p) + 4096
+            reqs.append(dict(params=p, f0=_f0(c, s), nsteps=c["steps"],
+                             out=torch.empty((c["nv"], c["nx"]), dtype=dt,
+                                             device=_device())))
+        srv = vp.Server(precision=case["precision"], max_active=64,
+                        pool_bytes=need + (4 << 20))
+        return dict(kind=kind, server=srv, requests=reqs)
+    if kind in ("run4", "snapshot4"):
+        g = vp4.VlasovRun4(precision=case["precision"], **_params4(case))
+        st = dict(kind=kind, run=g, f0=_f04(case, seed), steps=case["steps"])
+    else:
+        g = vp.VlasovRun(precision=case["precision"], **_params(case))
+        st = dict(kind=kind, run=g, f0=_f0(case, seed), steps=case["steps"])
+    if kind.startswith("snapshot"):
+        g.init_conditions(st["f0"])
+        g.step(st["steps"])
+    return st
+
+
+def run(state):
+    kind = state["kind"]
+    if kind == "poisson":
+        return vp.poisson_static(state["rho"], **state["kw"])
+    if kind == "serve":
+        state["server"].run(state["requests"])
+        return [r["out"] for r in state["requests"]]
+    g = state["run"]
+    if kind in ("run", "run4"):
+        g.init_conditions(state["f0"])
+        g.step(state["steps"])
+        f = g.reconstruct_f()
+        # in mixed precision rho holds no more than f does, which is float
+        return dict(f=f) if g.mixed else dict(f=f, rho=g.density())
+    return dict(f=g.reconstruct_f(), f_remap=g.reconstruct_f(1),
+                rho=g.density(), **g.diagnostics())
+
+
+# -------------------------------------------------------------------- work
+
+def _work_run(c, precision, evals):
+    """evals reconstructions of every site: four 34-flop candidate maps per
+    site; F_ini read and the elements' 12 doubles read and written each."""
+    n, e = c["nx"] * c["nv"], (c["nx"] // c["sx"]) * (c["nv"] // c["sv"])
+    fb = 4 if precision == "mixed" else 8
+    return (evals * (n * fb + e * 192) + n * (8 + 3 * fb),
+            evals * n * 136.0)
+
+
+def work(case):
+    kind = case["kind"]
+    if kind == "poisson":
+        return dict(bytes=32.0 * case["nx"], flops=12.0 * case["nx"])
+    if kind == "serve":
+        w = [_work_run(c, case["precision"], c["steps"] + 1)
+             for c, _ in _requests(case, 1)]
+        return dict(bytes=sum(x[0] for x in w), flops=sum(x[1] for x in w))
+    if kind in ("run", "snapshot"):
+        evals = case["steps"] + (case["precision"] == "fp64") + 1
+        b, f = _work_run(case, case["precision"],
+                         evals if kind == "run" else 4)
+        return dict(bytes=b, flops=f)
+    n = case["ns"] ** 2 * case["nv"] ** 2
+    e = (case["ns"] // case["ss"]) ** 2 * (case["nv"] // case["sv"]) ** 2
+    fb = 4 if case["precision"] == "mixed" else 8
+    evals = 4
+    if kind == "run4":
+        evals = case["steps"] + (case["precision"] == "fp64") + 1
+    return dict(bytes=evals * (n * fb + e * 960) + n * (8 + 3 * fb),
+                flops=evals * n * 3616.0)
+
+
+# ------------------------------------------------------------------- exact
+#
+# The method in float64 torch, written for clarity: every (element, site)
+# pair of a window around each element is formed, the nearest element of a
+# site is a scatter-minimum over them.
+
+PAIRS = 1 << 22  # (element, site) pairs at a time
+
+
+def _thomas(F, dim):
+    """Mirror-ended (1, 4, 1) solve c of 6 F along `dim`."""
+    f = 6.0 * F.movedim(dim, 0)
+    n = f.shape[0]
+    cp, d = [0.5], [f[0] * 0.25]
+    for i in range(1, n):
+        sub = 2.0 if i == n - 1 else 1.0
+        r = 1.0 / (4.0 - sub * cp[-1])
+        cp.append(r)
+        d.append((f[i] - sub * d[-1]) * r)
+    for i in range(n - 2, -1, -1):
+        d[i] = d[i] - cp[i] * d[i + 1]
+    return torch.stack(d).movedim(0, dim)
+
+
+def _cyclic(F, dim):
+    n = F.shape[dim]
+    k = torch.arange(n // 2 + 1, dtype=torch.float64, device=F.device)
+    lam = (4.0 + 2.0 * torch.cos(2.0 * math.pi * k / n)) / 6.0
+    shape = [1] * F.dim()
+    shape[dim] = -1
+    return torch.fft.irfft(torch.fft.rfft(F, dim=dim) / lam.reshape(shape),
+                           n=n, dim=dim)
+
+
+def _bspline(u):
+    t = 1.0 - u
+    return (t ** 3 / 6.0, (3.0 * u ** 3 - 6.0 * u ** 2 + 4.0) / 6.0,
+            (-3.0 * u ** 3 + 3.0 * u ** 2 + 3.0 * u + 1.0) / 6.0, u ** 3 / 6.0)
+
+
+def _kernel_w(x):
+    near = 1.0 - 1.5 * x ** 2 + 0.75 * x ** 3
+    far = 0.25 * (2.0 - x) ** 3
+    return torch.where(x <= 1.0, near, torch.where(x <= 2.0, far, 0.0 * x))
+
+
+class _Exact:
+    """What the 2D and the 4D run share.  Axes: na of them, the first np_
+    periodic when per; element arrays P (na, E), T (na, na, E), H (na, na,
+    na, E), symmetric in the last two."""
+
+    def __init__(self, n, s, lo, hi, per, beta=vp.BETA_PAPER):
+        self.n, self.s, self.lo, self.per, self.beta = n, s, lo, per, beta
+        self.na = len(n)
+        self.d = [(b - a) / m for a, b, m in zip(lo, hi, n)]
+        self.m = [a // b for a, b in zip(n, s)]
+        self.D = [a * b for a, b in zip(s, self.d)]
+        self.span = [b - a for a, b in zip(lo, hi)]
+        self.E = math.prod(self.m)
+        self.N = math.prod(n)
+        self.dev = _device()
+
+    def site(self, a, i):
+        return self.lo[a] + (i + 0.5) * self.d[a]
+
+    def lattice(self, e):
+        k = []
+        for a in range(self.na):
+            k.append(e % self.m[a])
+            e = torch.div(e, self.m[a], rounding_mode="floor")
+        return k
+
+    def lattice_q(self, a, k):
+        return self.site(a, self.s[a] * k + self.s[a] // 2)
+
+    def reset(self):
+        e = torch.arange(self.E, device=self.dev)
+        self.P = torch.stack([self.lattice_q(a, k.double())
+                              for a, k in enumerate(self.lattice(e))])
+        self.T = torch.eye(self.na, dtype=torch.float64, device=self.dev)
+        self.T = self.T[:, :, None].repeat(1, 1, self.E)
+        self.H = torch.zeros((self.na,) * 3 + (self.E,), dtype=torch.float64,
+                             device=self.dev)
+
+    def drift(self, h):
+        k = self.na // 2
+        self.P[:k] += h * self.P[k:]
+        for a in range(k):
+            if self.per[a]:
+                self.P[a] = self.lo[a] + torch.remainder(
+                    self.P[a] - self.lo[a], self.span[a])
+        self.T[:k] += h * self.T[k:]
+        self.H[:k] += h * self.H[k:]
+
+    def record(self):
+        self.A = torch.linalg.inv(self.T.permute(2, 0, 1).contiguous().cpu())
+        self.A = self.A.to(self.dev).permute(1, 2, 0).contiguous()
+
+    def image(self, a, d):
+        if self.per[a]:
+            d = d - self.span[a] * torch.round(d / self.span[a])
+        return d
+
+    def map(self, e, P):
+        """l and dQ of elements e at positions P (lists over the axes)."""
+        dp = [self.image(a, P[a] - self.P[a][e]) for a in range(self.na)]
+        A = [[self.A[a, b][e] for b in range(self.na)] for a in range(self.na)]
+        l = [sum(A[a][b] * dp[b] for b in range(self.na)) for a in range(self.na)]
+        u = []
+        for c in range(self.na):
+            u.append(sum(self.H[c, a, b][e] * (l[a] * l[b])
+                         for a in range(self.na) for b in range(self.na)))
+        dq = [l[a] - 0.5 * sum(A[a][b] * u[b] for b in range(self.na))
+              for a in range(self.na)]
+        return l, dq
+
+    def dist2(self, dq):
+        return sum((q / D) ** 2 for q, D in zip(dq, self.D))
+
+    def assign(self):
+        """Nearest valid element of every site (flat, x fastest), -1: none."""
+        self.record()
+        off = []
+        for a in range(self.na):
+            r = sum(self.T[a, b].abs() * self.D[b] for b in range(self.na))
+            k = int(math.ceil(float(r.max()) / self.d[a])) + 1
+            k = min(k, self.n[a] // 2 if self.per[a] else self.n[a])
+            off.append(torch.arange(-k, k + (0 if self.per[a] and 2 * k >= self.n[a] else 1),
+                                    device=self.dev))
+        grid = torch.meshgrid(*off, indexing="ij")
+        grid = [g.reshape(1, -1) for g in grid]
+        best = torch.full((self.N + 1,), math.inf, dtype=torch.float64,
+                          device=self.dev)
+        kept = []
+        step = max(1, PAIRS // grid[0].numel())
+        for e0 in range(0, self.E, step):
+            e = torch.arange(e0, min(self.E, e0 + step), device=self.dev)[:, None]
+            idx, ok, P, st = 0, True, [], 1
+            for a in range(self.na):
+                c = torch.round((self.P[a][e] - self.lo[a]) / self.d[a] - 0.5)
+                i = c.long() + grid[a]
+                if self.per[a]:
+                    i = torch.remainder(i, self.n[a])
+                ok = ok & (i >= 0) & (i < self.n[a])
+                P.append(self.site(a, i.double()))
+                idx = idx + i * st
+                st *= self.n[a]
+            l, dq = self.map(e.expand(-1, grid[0].shape[1]), P)
+            for a in range(self.na):
+                ok = ok & (l[a].abs() < self.D[a])
+            ok = ok.reshape(-1)
+            d2 = self.dist2(dq).reshape(-1)[ok]
+            idx = idx.reshape(-1)[ok]
+            ids = e.expand(-1, grid[0].shape[1]).reshape(-1)[ok]
+            best.scatter_reduce_(0, idx, d2, "amin")
+            kept.append((idx.int(), d2, ids.int()))
+        near = torch.full((self.N + 1,), self.E, dtype=torch.int64,
+                          device=self.dev)
+        for idx, d2, ids in kept:
+            hit = d2 == best[idx.long()]
+            near.scatter_reduce_(0, idx.long()[hit], ids.long()[hit], "amin")
+        near = near[:self.N]
+        return torch.where(near < self.E, near, -1)
+
+    def all_sites(self):
+        q, P = torch.arange(self.N, device=self.dev), []
+        for a in range(self.na):
+            P.append(self.site(a, (q % self.n[a]).double()))
+            q = torch.div(q, self.n[a], rounding_mode="floor")
+        return P
+
+    def index(self, a, Q):
+        return (Q - self.lo[a]) / self.d[a] - 0.5
+
+    def fetch(self, G, idx, mirror):
+        """G at integer sites: periodic axes wrap; others mirror, or 0."""
+        flat, ok, st = 0, None, 1
+        for a in range(self.na):
+            i, n = idx[a], self.n[a]
+            if self.per[a]:
+                i = torch.remainder(i, n)
+            elif mirror:
+                i = i.abs()
+                i = torch.where(i > n - 1, 2 * (n - 1) - i, i)
+            else:
+                o = (i >= 0) & (i < n)
+                ok = o if ok is None else ok & o
+            flat = flat + i.clamp(0, n - 1) * st
+            st *= n
+        v = G.reshape(-1)[flat]
+        return v if ok is None else torch.where(ok, v, torch.zeros_like(v))
+
+    def quadratic(self, s):
+        """Second-order interpolation of F_ini: nearest node, its axis
+        neighbours, one cross term per axis pair at the floor corner."""
+        near = [torch.floor(x + 0.5) for x in s]
+        low = [torch.floor(x).clamp(-1e6, 1e6).long() for x in s]
+        d = [x - n for x, n in zip(s, near)]
+        near = [n.clamp(-1e6, 1e6).long() for n in near]
+        at = lambda i: self.fetch(self.F, i, False)  # noqa: E731
+        f = at(near) * (1.0 - sum(x * x for x in d))
+        for a in range(self.na):
+            for sg in (1, -1):
+                i = list(near)
+                i[a] = near[a] + sg
+                f = f + at(i) * (0.5 * d[a] * (d[a] + sg))
+        for a in range(self.na):
+            for b in range(a + 1, self.na):
+                c = 0.0
+                for p in (0, 1):
+                    for q in (0, 1):
+                        i = list(near)
+                        i[a], i[b] = low[a] + p, low[b] + q
+                        c = c + (1.0 if p == q else -1.0) * at(i)
+                f = f + c * d[a] * d[b]
+        return f
+
+    def spline(self, s):
+        ok, low, w = True, [], []
+        for a in range(self.na):
+            i = torch.floor(s[a])
+            if not self.per[a]:
+                ok = ok & (s[a] >= 0.0) & (s[a] <= self.n[a] - 1.0)
+                i = i.clamp(0, self.n[a] - 2)
+            low.append(i.long())
+            w.append(_bspline(s[a] - i))
+        f = torch.zeros_like(s[0])
+        for q in range(4 ** self.na):
+            i, wt, r = [], 1.0, q
+            for a in range(self.na):
+                i.append(low[a] - 1 + r % 4)
+                wt = wt * w[a][r % 4]
+                r //= 4
+            f = f + wt * self.fetch(self.C, i, True)
+        return torch.where(ok, f, torch.zeros_like(f)) if torch.is_tensor(ok) else f
+
+    def fit(self):
+        C = self.F
+        for a in range(self.na):
+            C = (_cyclic if self.per[a] else _thomas)(C, self.na - 1 - a)
+        self.C = C
+
+    def zero_edges(self, f):
+        for a in range(self.na):
+            if not self.per[a]:
+                g = f.movedim(self.na - 1 - a, 0)
+                g[0] = 0.0
+                g[-1] = 0.0
+        return f
+
+    def init(self, f0):
+        self.F = self.zero_edges(f0.clone())
+        self.fit()
+        self.reset()
+
+    def transport(self):
+        near = self.assign()
+        e, P = near.clamp(min=0), self.all_sites()
+        _, dq = self.map(e, P)
+        k = self.lattice(e)
+        s = [self.index(a, self.lattice_q(a, k[a].double()) + dq[a])
+             for a in range(self.na)]
+        f = self.quadratic(s)
+        f = torch.where(near >= 0, f, torch.zeros_like(f))
+        return f.reshape(self.n[::-1])
+
+    def remap_f(self):
+        near = self.assign()
+        e, P = near.clamp(min=0), self.all_sites()
+        _, dq = self.map(e, P)
+        k0 = self.lattice(e)
+        z = [q / D for q, D in zip(dq, self.D)]
+        lo = [torch.where(x < self.beta, -1, 0) for x in z]
+        hi = [torch.where(x < -self.beta, 0, 1) for x in z]
+        three = False
+        for a in range(self.na):
+            three = three | (hi[a] - lo[a] == 2)
+        sw, sq = 0.0, [0.0] * self.na
+        for q in range(3 ** self.na):
+            o, r = [], q
+            for a in range(self.na):
+                o.append(r % 3 - 1)
+                r //= 3
+            use, flat, st, Qm = near >= 0, 0, 1, []
+            if sum(x != 0 for x in o) > 1:
+                use = use & ~three
+            for a in range(self.na):
+                use = use & (lo[a] <= o[a]) & (hi[a] >= o[a])
+                k = k0[a] + o[a]
+                Qm.append(self.lattice_q(a, k.double()))
+                if self.per[a]:
+                    k = torch.remainder(k, self.m[a])
+                else:
+                    use = use & (k >= 0) & (k < self.m[a])
+                flat = flat + k.clamp(0, self.m[a] - 1) * st
+                st *= self.m[a]
+            _, ex = self.map(flat, P)
+            w = _kernel_w(2.0 * torch.sqrt(self.dist2(ex)))
+            w = torch.where(use, w, torch.zeros_like(w))
+            sw = sw + w
+            for a in range(self.na):
+                sq[a] = sq[a] + w * (Qm[a] + ex[a])
+        s = []
+        for a in range(self.na):
+            own = self.lattice_q(a, k0[a].double()) + dq[a]
+            Q = torch.where(sw > 0.0, sq[a] / sw.clamp(min=1e-300), own)
+            s.append(self.index(a, Q))
+        f = self.spline(s)
+        f = torch.where(near >= 0, f, torch.zeros_like(f))
+        return self.zero_edges(f.reshape(self.n[::-1]))
+
+    def resample(self):
+        self.F = self.remap_f()
+        self.fit()
+        self.reset()
+
+    def kick(self, dt, a, g, h):
+        """v, T_v., H_v.. from the force, its gradient g[i][j] and second
+        derivatives h[i][j][k] at the elements."""
+        k = self.na // 2
+        T, H = self.T[:k].clone(), self.H[:k].clone()
+        for i in range(k):
+            self.P[k + i] += dt * a[i]
+            for j in range(k):
+                self.T[k + i] += dt * g[i][j] * T[j]
+                self.H[k + i] += dt * g[i][j] * H[j]
+                for l in range(k):
+                    self.H[k + i] += dt * h[i][j][l] * (T[j][:, None] * T[l][None])
+
+    def casimirs(self, f):
+        dv = math.prod(self.d)
+        lf = torch.where(f != 0.0, f * torch.log(f.abs().clamp(min=1e-300)),
+                         torch.zeros_like(f))
+        return -float(lf.sum()) * dv, dv
+
+
+class _Exact2(_Exact):
+    def __init__(self, p, steps):
+        super().__init__([p["nx"], p["nv"]], [p["sx"], p["sv"]],
+                         [p["x_min"], p["v_min"]], [p["x_max"], p["v_max"]],
+                         [bool(p["bc"]), False])
+        self.p, self.steps = p, steps
+
+    def density(self):
+        return self.d[1] * self.transport().sum(0)
+
+    def force(self, rho):
+        """a, a', a'' on the sites -4 .. nx + 3."""
+        n, G, dx = self.n[0], self.p["G"], self.d[0]
+        M = torch.cumsum(dx * rho, 0)
+        tot = M[-1]
+        if self.per[0]:
+            k = torch.arange(n, dtype=torch.float64, device=M.device)
+            left = torch.cat([M.new_zeros(1), M[:-1]])
+            B = tot * (2.0 * k + 1.0) / n - M - left
+            a = G * (B - B.mean())
+            a = a[torch.arange(-5, n + 5, device=M.device) % n]
+        else:
+            pad = torch.cat([M.new_zeros(6), M, tot.expand(6)])
+            a = G * ((tot - pad[1:]) - pad[:-1])
+        da = (a[2:] - a[:-2]) / (2.0 * dx)
+        d2 = ((a[2:] + a[:-2]) - 2.0 * a[1:-1]) / (dx * dx)
+        cut = (a.numel() - 2 - (n + 8)) // 2
+        return [t[cut:cut + n + 8] for t in (a[1:-1], da, d2)]
+
+    def tsc(self, tab):
+        u = self.index(0, self.P[0]).clamp(-3.0, self.n[0] + 2.0)
+        i = torch.floor(u + 0.5)
+        w = u - i
+        i = i.long() + 4
+        wt = (0.5 * (0.5 - w) ** 2, 0.75 - w * w, 0.5 * (0.5 + w) ** 2)
+        return [sum(wt[q] * t[i - 1 + q] for q in range(3)) for t in tab]
+
+    def next_dt(self, rho):
+        c, top = self.p.get("c_dyn", 0.0), float(rho.max())
+        if c <= 0.0 or top <= 0.0:
+            return self.p["dt"]
+        return min(self.p["dt"], c / math.sqrt(top))
+
+    def neighbour_gap(self):
+        """E_map: largest distance between the nearest element's prediction
+        and its four lattice neighbours' where their windows hold the site."""
+        near = self.assign()
+        e, P = near.clamp(min=0), self.all_sites()
+        _, dq = self.map(e, P)
+        k = self.lattice(e)
+        Q = [self.lattice_q(a, k[a].double()) + dq[a] for a in (0, 1)]
+        worst = 0.0
+        for o in ((-1, 0), (1, 0), (0, -1), (0, 1)):
+            use, kk = near >= 0, [k[0] + o[0], k[1] + o[1]]
+            Qm = [self.lattice_q(a, kk[a].double()) for a in (0, 1)]
+            for a in (0, 1):
+                if self.per[a]:
+                    kk[a] = torch.remainder(kk[a], self.m[a])
+                use = use & (kk[a] >= 0) & (kk[a] < self.m[a])
+                kk[a] = kk[a].clamp(0, self.m[a] - 1)
+            l, ex = self.map(kk[1] * self.m[0] + kk[0], P)
+            gap = torch.sqrt(self.dist2([Qm[a] + ex[a] - Q[a] for a in (0, 1)]))
+            use = use & (l[0].abs() < self.D[0]) & (l[1].abs() < self.D[1])
+            worst = max(worst, float(torch.where(use, gap, 0.0 * gap).max()))
+        return worst
+
+    def go(self, f0):
+        self.init(f0)
+        p = self.p
+        dt, self.t = self.next_dt(self.d[1] * self.F.sum(0)), 0.0
+        for k in range(1, self.steps + 1):
+            self.drift(0.5 * dt)
+            rho = self.density()
+            a, da, d2 = self.tsc(self.force(rho))
+            self.kick(dt, [a], [[da]], [[[d2]]])
+            self.drift(0.5 * dt)
+            self.t += dt
+            dt = self.next_dt(rho)
+            due = p["n_s"] > 0 and k % p["n_s"] == 0
+            if not due and p.get("emap_max", 0.0) > 0.0 and k % p["emap_every"] == 0:
+                due = self.neighbour_gap() > p["emap_max"]
+            if due:
+                self.resample()
+        self.dt = dt
+        return self
+
+    def diagnostics(self, f):
+        ent, cell = self.casimirs(f)
+        rho = self.d[1] * f.sum(0)
+        v = self.site(1, torch.arange(self.n[1], device=f.device).double())
+        a = self.force(rho)[0][4:-4]
+        G, M = self.p["G"], float(rho.sum()) * self.d[0]
+        pot = float((a * a - (0.0 if self.per[0] else (G * M) ** 2)).sum())
+        kin = 0.5 * float((f.sum(1) * v * v).sum()) * cell
+        pot = -pot * self.d[0] / (4.0 * G)
+        det = self.T[0, 0] * self.T[1, 1] - self.T[0, 1] * self.T[1, 0]
+        return dict(mass=M, e_kin=kin, e_pot=pot, energy=kin + pot, entropy=ent,
+                    max_det_dev=None, t=self.steps * self.p["dt"],
+                    step=None, overflow_blocks=None, emap=self.neighbour_gap(),
+                    dt=self.p["dt"], l1=float(f.abs().sum()) * cell,
+                    l2=math.sqrt(float((f * f).sum()) * cell))
+
+
+class _Exact4(_Exact):
+    def __init__(self, p, steps):
+        super().__init__([p["ns"]] * 2 + [p["nv"]] * 2, [p["ss"]] * 2 + [p["sv"]] * 2,
+                         [0.0, 0.0, -p["vmax"], -p["vmax"]],
+                         [p["L"], p["L"], p["vmax"], p["vmax"]],
+                         [True, True, False, False])
+        self.p, self.steps = p, steps
+
+    def density(self):
+        return self.d[2] ** 2 * self.transport().sum((0, 1))
+
+    def force(self, rho):
+        """(a_x, a_y) of div a = -2 G (rho - mean) on the periodic square."""
+        n = self.n[0]
+        k = torch.fft.fftfreq(n, 1.0 / n, dtype=torch.float64, device=rho.device)
+        k = 2.0 * math.pi * k / self.span[0]
+        kd = k.clone()
+        if n % 2 == 0:
+            kd[n // 2] = 0.0
+        k2 = k[None, :] ** 2 + k[:, None] ** 2
+        k2[0, 0] = 1.0
+        phi = -2.0 * self.p["G"] * torch.fft.fft2(rho) / k2
+        phi[0, 0] = 0.0
+        return [torch.fft.ifft2(-1j * w * phi).real for w in (kd[None, :], kd[:, None])]
+
+    def tsc(self, F):
+        out, ix, wt = 0.0, [], []
+        for a in (0, 1):
+            u = self.index(a, self.P[a])
+            i = torch.floor(u + 0.5)
+            w = u - i
+            ix.append(i.long())
+            wt.append((0.5 * (0.5 - w) ** 2, 0.75 - w * w, 0.5 * (0.5 + w) ** 2))
+        n = self.n[0]
+        for p in range(3):
+            for q in range(3):
+                out = out + wt[1][p] * wt[0][q] * F[(ix[1] - 1 + p) % n,
+                                                    (ix[0] - 1 + q) % n]
+        return out
+
+    def go(self, f0):
+        self.init(f0)
+        dt, dx = self.p["dt"], self.d[0]
+        sh = lambda A, i, j: torch.roll(A, (-j, -i), (0, 1))  # noqa: E731
+        for k in range(1, self.steps + 1):
+            self.drift(0.5 * dt)
+            acc, g, h = self.force(self.density()), [], []
+            for A in acc:
+                g.append([(sh(A, 1, 0) - sh(A, -1, 0)) / (2 * dx),
+                          (sh(A, 0, 1) - sh(A, 0, -1)) / (2 * dx)])
+                xy = (sh(A, 1, 1) - sh(A, 1, -1) - sh(A, -1, 1)
+                      + sh(A, -1, -1)) / (4 * dx * dx)
+                h.append([[(sh(A, 1, 0) + sh(A, -1, 0) - 2 * A) / (dx * dx), xy],
+                          [xy, (sh(A, 0, 1) + sh(A, 0, -1) - 2 * A) / (dx * dx)]])
+            self.kick(dt, [self.tsc(A) for A in acc],
+                      [[self.tsc(A) for A in r] for r in g],
+                      [[[self.tsc(A) for A in r] for r in q] for q in h])
+            self.drift(0.5 * dt)
+            if self.p["n_s"] > 0 and k % self.p["n_s"] == 0:
+                self.resample()
+        return self
+
+    def diagnostics(self, f):
+        ent, cell = self.casimirs(f)
+        v = self.site(2, torch.arange(self.n[2], device=f.device).double())
+        fv = f.sum((2, 3))
+        kin = 0.5 * float((fv * (v[:, None] ** 2 + v[None, :] ** 2)).sum()) * cell
+        ax, ay = self.force(self.d[2] ** 2 * f.sum((0, 1)))
+        pot = -float((ax * ax + ay * ay).sum()) * self.d[0] ** 2 / (4 * self.p["G"])
+        return dict(mass=float(f.sum()) * cell, e_kin=kin, e_pot=pot,
+                    energy=kin + pot, entropy=ent, t=self.steps * self.p["dt"])
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "poisson":
+        kw = _poisson_kw(case)
+        x = _Exact2(dict(kw, nx=case["nx"]), 0)
+        return tuple(t[4:-4] for t in x.force(_rho(case, seed)))
+    if kind == "serve":
+        # the smallest requests; the others would take too long
+        return [_Exact2(_params(c), c["steps"]).go(_f0(c, s)).transport()
+                if c["nx"] <= 256 else None for c, s in _requests(case, seed)]
+    if kind in ("run", "snapshot"):
+        if case["nx"] * case["nv"] * case["steps"] > 2.2e8:
+            return None
+        x = _Exact2(_params(case), case["steps"]).go(_f0(case, seed))
+    else:
+        if case["ns"] ** 2 * case["nv"] ** 2 > 1.1e6:
+            return None
+        x = _Exact4(_params4(case), case["steps"]).go(_f04(case, seed))
+    f = x.transport()
+    rho = math.prod(x.d[x.na // 2:]) * f.sum(tuple(range(x.na // 2)))
+    if kind in ("run", "run4"):
+        return dict(f=f) if case["precision"] == "mixed" else dict(f=f, rho=rho)
+    return dict(f=f, f_remap=x.remap_f(), rho=rho, **x.diagnostics(f))
