@@ -45,7 +45,7 @@ def listed():
         # ragged grid, variable step, resampling decided by E_map
         dict(name="adaptive_1020x1004_fp64", kind="run", nx=1020, nv=1004,
              sx=4, sv=4, steps=40, n_s=0, dt=1e-3, precision="fp64", bc=0,
-             c_dyn=8e-4, emap_max=2e-4, emap_every=10),
+             c_dyn=8e-4, emap_max=5e-5, emap_every=10),
         # the two-stream plasma on a ring, the same way
         dict(name="ring_2048_mixed", kind="run", nx=2048, nv=2048, sx=8, sv=8,
              steps=50, n_s=40, dt=0.05, precision="mixed", bc=1, c_dyn=0.0,
