@@ -66,6 +66,8 @@ KP make_kp(const vp4_params *p) {
     k.nb[a] = (n - 1 - k.o[a]) / BLK + k.ob[a] + 1;
   }
   k.nls = p->ns / BLK;
+  k.inv_ms = 1.0 / k.ms;
+  k.inv_mv = 1.0 / k.mv;
   k.cap = list_cap(p->ss, p->sv);
   k.L = p->L;
   k.hL = 0.5 * p->L;
@@ -102,7 +104,7 @@ Layout make_layout(const vp4_params *p, const KP &k) {
   L.fs = take(N4 * fb);
   L.st = take((size_t)NST * k.E * 8);
   L.rec = take((size_t)RS * k.E * 8);
-  L.cnt = take((size_t)L.nl * 4);
+  L.cnt = take((size_t)2 * L.nl * 4);  // two count buffers, see vp4_ctx::cur
   L.lst = take((size_t)L.nl * k.cap * 4);
   L.flags = take(64);
   L.part = take((size_t)k.nb[2] * k.nb[3] * n2 * 8);
@@ -136,6 +138,8 @@ struct vp4_ctx {
   char *ws;
   int64_t step = 0;
   bool ready = false;
+  int cur = 0;  // the count buffer of the live lists; both are zero whenever
+                // a call returns
   std::string err;
   std::vector<char> host_tab;
   bool prof = false;
@@ -147,6 +151,7 @@ struct vp4_ctx {
     return reinterpret_cast<T *>(ws + off);
   }
   bool mixed() const { return p.precision == VP4_MIXED; }
+  int *counts(int which) const { return at<int>(L.cnt) + (size_t)which * L.nl; }
 };
 
 namespace {
@@ -187,31 +192,39 @@ unsigned grid_for(long long n, int bs) {
 
 int zero_counts(vp4_ctx *c) {
   hipLaunchKernelGGL(k4_zero, dim3(grid_for(std::min<long long>(c->L.nl, 1 << 22), 256)),
-                     dim3(256), 0, c->stream, c->at<int>(c->L.cnt), c->L.nl);
+                     dim3(256), 0, c->stream, c->counts(c->cur), c->L.nl);
   VP4_CHECK(c, "k4_zero");
+  return VP4_OK;
+}
+
+// The element pass: kick + corrector, predictor drift, records and lists
+// into count buffer reg_buf; clears count buffer zero_buf (-1: none).
+int launch_elem(vp4_ctx *c, int kick, int drift, int predict, int reg_buf,
+                int zero_buf) {
+  Prof ps(c, kick ? PK_KICK : PK_PREDICT);
+  hipLaunchKernelGGL(k4_elem, dim3(grid_for(c->k.E, EPW)), dim3(256), 0,
+                     c->stream, c->k, c->at<double>(c->L.st),
+                     c->at<double>(c->L.fld), c->at<double>(c->L.rec),
+                     zero_buf >= 0 ? c->counts(zero_buf) : nullptr,
+                     zero_buf >= 0 ? c->L.nl : 0, c->counts(reg_buf),
+                     c->at<int>(c->L.lst), c->at<int>(c->L.flags), kick, drift,
+                     predict);
+  VP4_CHECK(c, "k4_elem");
   return VP4_OK;
 }
 
 // Records and block lists for the current elements (after the predictor's
 // half drift when `drift`).
 int predict(vp4_ctx *c, int drift) {
-  int rc;
-  if ((rc = zero_counts(c))) return rc;
-  Prof ps(c, PK_PREDICT);
-  hipLaunchKernelGGL(k4_predict, dim3(grid_for(c->k.E, 256)), dim3(256), 0,
-                     c->stream, c->k, c->at<double>(c->L.st),
-                     c->at<double>(c->L.rec), c->at<int>(c->L.cnt),
-                     c->at<int>(c->L.lst), c->at<int>(c->L.flags), drift, 1);
-  VP4_CHECK(c, "k4_predict");
-  return VP4_OK;
+  return launch_elem(c, 0, drift, 1, c->cur, -1);
 }
 
 template <typename FT, int MODE>
 int recon_t(vp4_ctx *c, void *fout, int *aout) {
   Prof ps(c, PK_RECON);
   hipLaunchKernelGGL((k4_recon<FT, MODE>), dim3((unsigned)c->L.nb), dim3(256),
-                     0, c->stream, c->k, c->at<double>(c->L.rec),
-                     c->at<int>(c->L.cnt), c->at<int>(c->L.lst),
+                     c->k.cap * QUERY_SLOT_BYTES, c->stream, c->k, c->at<double>(c->L.rec),
+                     c->counts(c->cur), c->at<int>(c->L.lst),
                      c->at<int>(c->L.flags), c->at<FT>(c->L.F),
                      c->at<double>(c->L.part), reinterpret_cast<FT *>(fout),
                      aout);
@@ -292,9 +305,9 @@ int reset(vp4_ctx *c) {
 template <typename FT>
 int remap_eval_t(vp4_ctx *c, void *out) {
   Prof ps(c, PK_REMAP);
-  hipLaunchKernelGGL((k4_remap<FT>), dim3((unsigned)c->L.nb), dim3(256), 0,
-                     c->stream, c->k, c->at<double>(c->L.rec),
-                     c->at<int>(c->L.cnt), c->at<int>(c->L.lst),
+  hipLaunchKernelGGL((k4_remap<FT>), dim3((unsigned)c->L.nb), dim3(256),
+                     c->k.cap * QUERY_SLOT_BYTES, c->stream, c->k, c->at<double>(c->L.rec),
+                     c->counts(c->cur), c->at<int>(c->L.lst),
                      c->at<int>(c->L.flags), c->at<FT>(c->L.C),
                      reinterpret_cast<FT *>(out));
   VP4_CHECK(c, "k4_remap");
@@ -309,25 +322,29 @@ int do_remap(vp4_ctx *c) {
   int rc;
   if ((rc = predict(c, 0))) return rc;
   if ((rc = remap_eval(c, c->ws + c->L.F))) return rc;
+  if ((rc = zero_counts(c))) return rc;
   if ((rc = fit(c))) return rc;
   return reset(c);
 }
 
+// n steps.  The kick + corrector of a step and the predictor of the next
+// share one element pass, which also clears the counts that the
+// reconstruction has used, unless a resampling or the end of the call comes
+// between them: the elements are at integer time, and both count buffers
+// zero, whenever control returns to the caller.
 int run_steps(vp4_ctx *c, int n) {
   int rc;
+  bool predicted = false;
   for (int s = 0; s < n; ++s) {
-    if ((rc = predict(c, 1))) return rc;
+    if (!predicted && (rc = predict(c, 1))) return rc;
     if ((rc = density_field(c, nullptr))) return rc;
-    {
-      Prof ps(c, PK_KICK);
-      hipLaunchKernelGGL(k4_kick, dim3(grid_for(c->k.E, 256)), dim3(256), 0,
-                         c->stream, c->k, c->at<double>(c->L.st),
-                         c->at<double>(c->L.fld));
-      VP4_CHECK(c, "k4_kick");
-    }
     c->step += 1;
-    if (c->p.n_s > 0 && c->step % c->p.n_s == 0 && (rc = do_remap(c)))
+    const bool remap = c->p.n_s > 0 && c->step % c->p.n_s == 0;
+    predicted = !remap && s + 1 < n;
+    if ((rc = launch_elem(c, 1, predicted, predicted, c->cur ^ 1, c->cur)))
       return rc;
+    if (predicted) c->cur ^= 1;
+    if (remap && (rc = do_remap(c))) return rc;
   }
   return VP4_OK;
 }
@@ -510,7 +527,8 @@ int vp4_reconstruct_f(vp4_ctx *c, int scheme, void *f_out) {
   if (!c->ready) return VP4_ESTATE;
   int rc;
   if ((rc = predict(c, 0))) return rc;
-  return scheme == 0 ? recon<M_F>(c, f_out, nullptr) : remap_eval(c, f_out);
+  rc = scheme == 0 ? recon<M_F>(c, f_out, nullptr) : remap_eval(c, f_out);
+  return rc ? rc : zero_counts(c);
 }
 
 int vp4_density(vp4_ctx *c, double *rho) {
@@ -518,7 +536,8 @@ int vp4_density(vp4_ctx *c, double *rho) {
   if (!c->ready) return VP4_ESTATE;
   int rc;
   if ((rc = predict(c, 0))) return rc;
-  return density_field(c, rho);
+  if ((rc = density_field(c, rho))) return rc;
+  return zero_counts(c);
 }
 
 int vp4_field(vp4_ctx *c, const double *rho, double *ax, double *ay) {
@@ -542,6 +561,7 @@ int vp4_diagnostics(vp4_ctx *c, double *out) {
   if ((rc = predict(c, 0))) return rc;
   if ((rc = density_field(c, nullptr))) return rc;
   if ((rc = recon<M_F>(c, c->ws + c->L.fs, nullptr))) return rc;
+  if ((rc = zero_counts(c))) return rc;
   if (c->mixed())
     hipLaunchKernelGGL((k4_diag_part<float>), dim3(NDIAG), dim3(256), 0,
                        c->stream, c->k, c->at<float>(c->L.fs),
@@ -585,7 +605,8 @@ int vp4_get_assignment(vp4_ctx *c, int32_t *a) {
   if (!c->ready) return VP4_ESTATE;
   int rc;
   if ((rc = predict(c, 0))) return rc;
-  return recon<M_ASSIGN>(c, nullptr, a);
+  if ((rc = recon<M_ASSIGN>(c, nullptr, a))) return rc;
+  return zero_counts(c);
 }
 
 int vp4_prof_begin(vp4_ctx *c, int max_launches) {

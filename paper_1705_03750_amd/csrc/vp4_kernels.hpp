@@ -10,7 +10,9 @@
 //   F, C, f  [nv][nv][ns][ns] (x fastest): F_ini, spline coefficients and a
 //            scratch f; no padding -- the interpolations wrap x and y and
 //            treat u and w as zero (F) or mirrored (C) outside the grid.
-//   state    SoA [60][E]; rec AoS [E][60]: X (4), A = T^-1 (16), H (40).
+//   state    SoA [60][E]; rec AoS [E][64]: X (4), A = T^-1 (16), the
+//            element's cull constants (R_K, R_DELTA; two words unused), and
+//            -H/2 with the off-diagonal terms doubled (40).
 //   lists    per query block of 4^4 sites: a count and cap element ids;
 //            every element whose validity window can reach a site of the
 //            block is listed.  Block boundaries sit half an element spacing
@@ -30,10 +32,10 @@ namespace vp4k {
 
 constexpr int NST = 60;
 constexpr int S_P = 0, S_T = 4, S_H = 20;  // state rows
-constexpr int RS = 60;                     // record doubles
+constexpr int RS = 64;                     // record doubles (512 bytes)
+constexpr int R_A = 4, R_K = 20, R_DELTA = 21, R_G = 24;  // record offsets
 constexpr int BLK = 4;                     // sites per axis of a block
 constexpr int SPAN = 4096;                 // max blocks of one element
-constexpr int STAGE = 32;                  // records staged per round
 enum { FL_NUMERIC = 1, FL_WIDE = 2 };
 enum { M_DENSITY = 0, M_F = 1, M_ASSIGN = 2 };
 
@@ -49,7 +51,9 @@ struct KP {
   int nls;       // list columns per space axis (ns / 4)
   int cap;       // list slots per block
   double L, hL, vmax, dx, du, inv_dx, inv_du, G, dt, h, beta;
-  double Dm[4], rD[4];
+  double inv_ms, inv_mv;  // 1 / ms, 1 / mv (lat_index)
+  double Dm[4], rD[4];  // element spacings and their inverses; the two space
+                        // axes' are equal, and the two velocity axes'
 };
 
 __device__ __forceinline__ double coord(const KP &p, int a, int i) {
@@ -59,13 +63,19 @@ __device__ __forceinline__ double lat_q(const KP &p, int a, int k) {
   const int s = a < 2 ? p.ss : p.sv;
   return coord(p, a, s * k + s / 2);
 }
+// Lattice indices of element e < 2^24: the quotients by ms and mv (at most
+// 2^9) from a multiplication, (e + 1/2) / m being at least 2^-10 away from
+// an integer.
 __device__ __forceinline__ void lat_index(const KP &p, int e, int k[4]) {
-  k[0] = e % p.ms;
-  e /= p.ms;
-  k[1] = e % p.ms;
-  e /= p.ms;
-  k[2] = e % p.mv;
-  k[3] = e / p.mv;
+  int q = (int)(((double)e + 0.5) * p.inv_ms);
+  k[0] = e - q * p.ms;
+  e = q;
+  q = (int)(((double)e + 0.5) * p.inv_ms);
+  k[1] = e - q * p.ms;
+  e = q;
+  q = (int)(((double)e + 0.5) * p.inv_mv);
+  k[2] = e - q * p.mv;
+  k[3] = q;
 }
 __device__ __forceinline__ double wrapL(const KP &p, double x) {
   if (x < 0.0) {
@@ -102,6 +112,13 @@ __device__ __forceinline__ long long list_of(const KP &p, int bx, int by, int bu
   return (((long long)bw * p.nb[2] + bu) * p.nls + ly) * p.nls + lx;
 }
 
+// LDS written by a lane of the wavefront, read by another.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ------------------------------------------------------------- elements
 
 __global__ __launch_bounds__(256) void k4_reset(KP p, double *__restrict__ st) {
@@ -122,22 +139,6 @@ __global__ __launch_bounds__(256) void k4_zero(int *__restrict__ a, long long n)
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += gsz)
     a[i] = 0;
-}
-
-// Drift over h of the state held in s[60] (section 2.4 per space axis):
-// x_i += h v_i (then the periodic wrap), T_i. += h T_{i+2}., H_i.. += h
-// H_{i+2}...
-__device__ __forceinline__ void drift4(const KP &p, double *s, double h) {
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    s[S_P + i] = wrapL(p, fma(h, s[S_P + i + 2], s[S_P + i]));
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      s[S_T + 4 * i + j] = fma(h, s[S_T + 4 * (i + 2) + j], s[S_T + 4 * i + j]);
-#pragma unroll
-    for (int q = 0; q < 10; ++q)
-      s[S_H + 10 * i + q] = fma(h, s[S_H + 10 * (i + 2) + q], s[S_H + 10 * i + q]);
-  }
 }
 
 // A = T^-1 by the adjugate (2 x 2 minors of rows 0-1 and rows 2-3); false
@@ -177,28 +178,100 @@ __device__ __forceinline__ bool inv4(const double *m, double *r, double &det) {
   return true;
 }
 
-// Can the validity window of the element (record r) hold a site of the
+// One field of the force at (x, y): 3 x 3 dual TSC.
+__device__ __forceinline__ double tsc_field(const KP &p,
+                                            const double *__restrict__ A,
+                                            double x, double y) {
+  const int n = p.ns;
+  double u[2] = {x * p.inv_dx - 0.5, y * p.inv_dx - 0.5};
+  double w[2][3];
+  int at[2][3];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    if (!(u[a] >= -3.0)) u[a] = -3.0;
+    if (u[a] > (double)n + 2.0) u[a] = (double)n + 2.0;
+    const double fi = floor(u[a] + 0.5), d = u[a] - fi;
+    const double tm = 0.5 - d, tp = 0.5 + d;
+    w[a][0] = 0.5 * (tm * tm);
+    w[a][1] = 0.75 - d * d;
+    w[a][2] = 0.5 * (tp * tp);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      // sites in [-4, n + 3] and n >= 8: at most one period off
+      const int i = (int)fi - 1 + q;
+      at[a][q] = i < 0 ? i + n : (i >= n ? i - n : i);
+    }
+  }
+  double row[3];
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    const double *R = A + (size_t)at[1][b] * n;
+    row[b] = fma(w[0][2], R[at[0][2]],
+                 fma(w[0][1], R[at[0][1]], w[0][0] * R[at[0][0]]));
+  }
+  return fma(w[1][2], row[2], fma(w[1][1], row[1], w[1][0] * row[0]));
+}
+
+// The element pass (section 2.4): kick over dt and corrector drift (when
+// `kick`), predictor drift (when `drift`), then (when `predict`) the inverse,
+// the query record and the registration in every block the validity window
+// can reach, counted in cnt_reg; cnt_zero (nzero counts) is cleared.
+//
+// A workgroup takes EPW consecutive elements with their states in LDS, and
+// its threads the entries of the states (the kick and the drifts act entry by
+// entry), then the (element, block) pairs of the registration.  One thread
+// per element kept 60 entries in registers and walked its 81 or more blocks
+// one after another, each with an atomic to wait for: 159 us at 64^4 (65536
+// elements) and 126 us at 16^4 (256), against 97 and 15 us on average for this
+// pass, the kick (18 and 9 us as its own launch) included.  It waits on the
+// slot claims' device atomics.
+constexpr int EPW = 16;
+constexpr int EP1 = EPW + 1;  // LDS pitch
+constexpr int REG_AHEAD = 4;  // pairs in flight per thread
+struct ElemLds {
+  double s[NST][EP1], A[16][EP1], f[12][EP1], u[4][EP1];
+  double k[EPW], delta[EPW];
+  int blo[4][EP1], ext[4][EP1], at[EP1];
+};
+
+// Entry r of the 30 that a drift (or a kick) changes: its state row and the
+// row of its rate (a drift adds h times the velocity row).
+__device__ __forceinline__ void moving_row(int r, int &space, int &vel) {
+  if (r < 2) {
+    space = S_P + r;
+    vel = space + 2;
+  } else if (r < 10) {
+    space = S_T + r - 2;
+    vel = space + 8;
+  } else {
+    space = S_H + r - 10;
+    vel = space + 20;
+  }
+}
+
+// Can the validity window of element e of the workgroup hold a site of the
 // block whose sites span [g0, g1] per axis (space columns unwrapped)?  l = A dP is
 // linear, so over the block's box each l_a ranges over its centre value +-
 // sum_b |A_ab| half-width_b; rounding margins as in the 2D engine.
-__device__ __forceinline__ bool block_meets(const KP &p, const double *r,
-                                            const int g0[4], const int g1[4]) {
+__device__ __forceinline__ bool block_meets(const KP &p, const ElemLds &S,
+                                            int e, const int g0[4],
+                                            const int g1[4]) {
   double m[4], h[4];
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     const double lo = coord(p, a, g0[a]), hi = coord(p, a, g1[a]);
-    m[a] = 0.5 * (lo + hi) - r[a];
+    m[a] = 0.5 * (lo + hi) - S.s[S_P + a][e];
     h[a] = 0.5 * (hi - lo);
   }
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
-    const double *A = r + 4 + 4 * a;
     double c = 0.0, rad = 0.0, mag = 0.0;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      c = fma(A[b], m[b], c);
-      rad = fma(fabs(A[b]), h[b], rad);
-      mag = fma(fabs(A[b]), fabs(m[b]) + h[b] + 1.0, mag);
+      const double A = S.A[4 * a + b][e];
+      c = fma(A, m[b], c);
+      rad = fma(fabs(A), h[b], rad);
+      mag = fma(fabs(A), fabs(m[b]) + h[b] + 1.0, mag);
     }
     const double tol = 0x1p-36 * (mag + p.Dm[a]);
     if (!(fabs(c) - rad < p.Dm[a] + tol)) return false;
@@ -206,218 +279,528 @@ __device__ __forceinline__ bool block_meets(const KP &p, const double *r,
   return true;
 }
 
-// Predictor drift (when `drift`), inverse and query record of every
-// element, and (when `reg`) its registration in every block its window can
-// reach.  Counts must be zero on entry.
-__global__ __launch_bounds__(256) void k4_predict(
-    KP p, double *__restrict__ st, double *__restrict__ rec,
-    int *__restrict__ cnt, int *__restrict__ lst, int *__restrict__ flags,
-    int drift, int reg) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= p.E) return;
+__global__ __launch_bounds__(256) void k4_elem(
+    KP p, double *__restrict__ st, const double *__restrict__ fld,
+    double *__restrict__ rec, int *__restrict__ cnt_zero, long long nzero,
+    int *__restrict__ cnt_reg, int *__restrict__ lst, int *__restrict__ flags,
+    int kick, int drift, int predict) {
+  __shared__ ElemLds S;
+  const int tid = threadIdx.x;
+  const long long gsz = (long long)gridDim.x * 256;
+  for (long long i = (long long)blockIdx.x * 256 + tid; i < nzero; i += gsz)
+    cnt_zero[i] = 0;
+  const int e0 = blockIdx.x * EPW, ne = min(EPW, p.E - e0);
+  if (ne <= 0) return;
   const size_t E = (size_t)p.E;
-  double s[NST];
-#pragma unroll
-  for (int q = 0; q < NST; ++q) s[q] = st[q * E + e];
-  if (drift) {
-    drift4(p, s, p.h);
-#pragma unroll
-    for (int q = 0; q < 40; ++q) st[q * E + e] = s[q];
+  for (int q = tid; q < NST * EPW; q += 256) {
+    const int r = q / EPW, e = q % EPW;
+    if (e < ne) S.s[r][e] = st[r * E + e0 + e];
   }
-  double A[16], det;
-  const bool ok = inv4(s + S_T, A, det);
-  double *r = rec + (size_t)e * RS;
-#pragma unroll
-  for (int a = 0; a < 4; ++a) r[a] = s[S_P + a];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) r[4 + q] = ok ? A[q] : 0.0;
-#pragma unroll
-  for (int q = 0; q < 40; ++q) r[20 + q] = s[S_H + q];
-  bool bad = !ok;
-#pragma unroll
-  for (int a = 0; a < 4; ++a) bad = bad || !isfinite(s[S_P + a]);
-  if (bad) {
-    atomicOr(flags, FL_NUMERIC);
-    return;
+  __syncthreads();
+  if (kick) {
+    const int k = tid / EPW, e = tid % EPW;
+    if (k < 12 && e < ne)
+      S.f[k][e] = tsc_field(p, fld + (size_t)k * p.ns * p.ns, S.s[S_P][e],
+                            S.s[S_P + 1][e]);
+    __syncthreads();
+    // v, T_v. and H_v.. (reading R5: the right-hand sides use the half-step
+    // T and H of the space rows, which the kick leaves alone)
+    const double dt = p.dt;
+    for (int q = tid; q < 30 * EPW; q += 256) {
+      const int r = q / EPW, e = q % EPW;
+      if (e >= ne) continue;
+      int space, vel;
+      moving_row(r, space, vel);
+      double v;
+      int i;
+      if (r < 2) {
+        v = S.f[r][e];
+      } else if (r < 10) {
+        i = (r - 2) >> 2;
+        const int j = (r - 2) & 3;
+        v = fma(S.f[3 + 2 * i][e], S.s[S_T + 4 + j][e],
+                S.f[2 + 2 * i][e] * S.s[S_T + j][e]);
+      } else {
+        i = (r - 10) / 10;
+        const int h = (r - 10) % 10, jb = PB[h], kc = PC[h];
+        const double t0j = S.s[S_T + jb][e], t1j = S.s[S_T + 4 + jb][e];
+        const double t0k = S.s[S_T + kc][e], t1k = S.s[S_T + 4 + kc][e];
+        v = S.f[2 + 2 * i][e] * S.s[S_H + h][e];
+        v = fma(S.f[3 + 2 * i][e], S.s[S_H + 10 + h][e], v);
+        v = fma(S.f[6 + 3 * i][e], t0j * t0k, v);
+        v = fma(S.f[7 + 3 * i][e], fma(t0j, t1k, t1j * t0k), v);
+        v = fma(S.f[8 + 3 * i][e], t1j * t1k, v);
+      }
+      const double x = fma(dt, v, S.s[vel][e]);
+      S.s[vel][e] = x;
+      st[vel * E + e0 + e] = x;
+    }
+    __syncthreads();
   }
-  if (!reg) return;
-  // Eulerian reach per axis: |dP_a| <= sum_b |T_ab| Dm_b, in sites, with
-  // a relative margin for the rounding of l = A dP
-  int blo[4], bhi[4];
+  if (kick || drift) {
+    // the corrector and the next predictor as two roundings, as two passes
+    for (int q = tid; q < 30 * EPW; q += 256) {
+      const int r = q / EPW, e = q % EPW;
+      if (e >= ne) continue;
+      int space, vel;
+      moving_row(r, space, vel);
+      const double v = S.s[vel][e];
+      double x = S.s[space][e];
+      for (int t = 0; t < kick + drift; ++t) {
+        x = fma(p.h, v, x);
+        if (r < 2) x = wrapL(p, x);
+      }
+      S.s[space][e] = x;
+      st[space * E + e0 + e] = x;
+    }
+    __syncthreads();
+  }
+  if (!predict) return;
+  int bad = 0;
+  double det = 1.0;
+  if (tid < EPW) {
+    // A = T^-1, one thread per element
+    double T[16], A[16];
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
+    for (int q = 0; q < 16; ++q) T[q] = tid < ne ? S.s[S_T + q][tid] : 0.0;
+    bad = !inv4(T, A, det);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) S.A[q][tid] = bad ? 0.0 : A[q];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) bad = bad || !isfinite(S.s[S_P + a][tid]);
+    if (tid < ne && bad) atomicOr(flags, FL_NUMERIC);
+  }
+  if (tid < 64) {
+    // four threads per element, one per axis (wavefront 0)
+    const int e = tid >> 2, a = tid & 3;
+    bad = __shfl(bad, e);
+    det = __shfl(det, e);
+    wave_sync();
+    double x = 0.0;
+#pragma unroll
+    for (int q = 0; q < 10; ++q)
+      x += (PB[q] == PC[q] ? 0.5 : 1.0) * fabs(S.s[S_H + 10 * a + q][e]) *
+           (p.Dm[PB[q]] * p.Dm[PC[q]]);
+    S.u[a][e] = x;
+    wave_sync();
+    // Bound of the map's quadratic part, for the query's cull.  On the
+    // validity window |l_a| < Dm_a, |u_c| <= sum_bd |H_cbd| Dm_b Dm_d, and
+    // the Lagrangian distance between dQ = l - A u / 2 and l (element
+    // spacings) is at most delta = |rD_a sum_c |A_ac| |u_c| / 2|, so |z(dQ)|
+    // >= |z(l)| - delta.  A site whose best squared distance is bd cannot
+    // take the element when |z(l)|^2 > (sqrt(bd) + delta)^2; with 2 delta
+    // sqrt(bd) <= delta (1 + bd) it is enough that |z(l)|^2 k - delta > bd,
+    // k = 1 / (1 + delta).  The margins (2^-20 relative and 2^-36 absolute
+    // on delta, 2^-30 on k) exceed the rounding of dQ and of the test by
+    // far, so a culled element loses strictly.
+    double t = 0.0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) t += fabs(S.A[4 * a + c][e]) * S.u[c][e];
+    t *= p.rD[a];
+    t *= t;
+    t += __shfl_xor(t, 1);
+    t += __shfl_xor(t, 2);
+    const double delta = sqrt(t) * (1.0 + 0x1p-20) + 0x1p-36;
+    if (a == 0) {
+      S.delta[e] = delta;
+      S.k[e] = (1.0 - 0x1p-30) / (1.0 + delta);
+    }
+    // Eulerian reach along the axis: |dP_a| <= sum_b |T_ab| Dm_b, in sites,
+    // with a relative margin for the rounding of l = A dP
     double reach = 0.0, tsum = 0.0;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      reach = fma(fabs(s[S_T + 4 * a + b]), p.Dm[b], reach);
-      tsum += fabs(s[S_T + 4 * a + b]);
+      const double v = fabs(S.s[S_T + 4 * a + b][e]);
+      reach = fma(v, p.Dm[b], reach);
+      tsum += v;
     }
     const double rel = 0x1p-20 + 0x1p-40 * (tsum * tsum) * fabs(1.0 / det);
     const double inv_d = a < 2 ? p.inv_dx : p.inv_du;
     const double rs = reach * inv_d * (1.0 + rel) + 0x1p-20;
-    const double c = (a < 2 ? s[S_P + a] : s[S_P + a] + p.vmax) * inv_d - 0.5;
+    const double X = S.s[S_P + a][e];
+    const double c = (a < 2 ? X : X + p.vmax) * inv_d - 0.5;
     int lo = (int)ceil(c - rs), hi = (int)floor(c + rs);
     if (a >= 2) {
       lo = max(lo, 0);
       hi = min(hi, p.nv - 1);
-      if (lo > hi) return;
-    } else if (!(rs < 0.5 * (double)p.ns - 2.0 * BLK) ||
-               hi - lo > p.ns - 3 * BLK) {
-      atomicOr(flags, FL_WIDE);  // too wide for nearest-image lists
-      return;
+    } else {
+      // nearest images lie within half a period; a window reaching further
+      // enters every list column (the seam's twice: a harmless repetition)
+      lo = max(lo, (int)floor(c) - p.ns / 2);
+      hi = min(hi, (int)ceil(c) + p.ns / 2);
     }
-    blo[a] = blk_of(p, a, lo);  // unwrapped on x and y
-    bhi[a] = blk_of(p, a, hi);
+    const int b0 = blk_of(p, a, lo), n = blk_of(p, a, hi) - b0 + 1;
+    S.blo[a][e] = b0;  // unwrapped on x and y
+    S.ext[a][e] = n;
+    // the blocks of the element's box: none for a bad element or a window
+    // off the grid; too many of them: the queries scan every element
+    int box = (e >= ne || bad || lo > hi) ? 0 : min(n, SPAN + 1);
+    int m = __shfl_xor(box, 1);
+    box = min(box * m, SPAN + 1);
+    m = __shfl_xor(box, 2);
+    box = min(box * m, SPAN + 1);
+    if (a == 0) {
+      if (box > SPAN) {
+        atomicOr(flags, FL_WIDE);
+        box = 0;
+      }
+      S.at[e] = box;
+    }
+    wave_sync();
+    // first pair of every element
+    if (tid == 0) {
+      int sum = 0;
+      for (int q = 0; q < EPW; ++q) {
+        const int b = S.at[q];
+        S.at[q] = sum;
+        sum += b;
+      }
+      S.at[EPW] = sum;
+    }
   }
-  const long long nblk = (long long)(bhi[0] - blo[0] + 1) *
-                         (bhi[1] - blo[1] + 1) * (bhi[2] - blo[2] + 1) *
-                         (bhi[3] - blo[3] + 1);
-  if (nblk > SPAN) {
-    atomicOr(flags, FL_WIDE);
-    return;
+  __syncthreads();
+  for (int q = tid; q < RS * ne; q += 256) {
+    const int e = q / RS, o = q % RS;
+    double v = 0.0;
+    if (o < R_A)
+      v = S.s[S_P + o][e];
+    else if (o < R_K)
+      v = S.A[o - R_A][e];
+    else if (o == R_K)
+      v = S.k[e];
+    else if (o == R_DELTA)
+      v = S.delta[e];
+    else if (o >= R_G)
+      v = (PB[(o - R_G) % 10] == PC[(o - R_G) % 10] ? -0.5 : -1.0) *
+          S.s[S_H + o - R_G][e];
+    rec[(size_t)(e0 + e) * RS + o] = v;
   }
-  int b[4], g0[4], g1[4];
-  for (b[3] = blo[3]; b[3] <= bhi[3]; ++b[3])
-    for (b[2] = blo[2]; b[2] <= bhi[2]; ++b[2])
-      for (b[1] = blo[1]; b[1] <= bhi[1]; ++b[1])
-        for (b[0] = blo[0]; b[0] <= bhi[0]; ++b[0]) {
-          for (int a = 0; a < 4; ++a) {
-            g0[a] = blk_first(p, a, b[a]);
-            g1[a] = g0[a] + BLK - 1;
-            if (a >= 2) {  // the live sites of a partial velocity block
-              g0[a] = max(g0[a], 0);
-              g1[a] = min(g1[a], p.nv - 1);
-            }
-          }
-          if (!block_meets(p, r, g0, g1)) continue;
-          const long long blk = list_of(p, b[0], b[1], b[2], b[3]);
-          const int slot = atomicAdd(&cnt[blk], 1);
-          if (slot < p.cap) lst[blk * p.cap + slot] = e;
+  const int total = S.at[EPW];
+  for (int q0 = tid; q0 < total; q0 += 256 * REG_AHEAD) {
+    long long blk[REG_AHEAD];
+    int id[REG_AHEAD], slot[REG_AHEAD];
+#pragma unroll
+    for (int k = 0; k < REG_AHEAD; ++k) {
+      const int q = q0 + 256 * k;
+      blk[k] = -1;
+      if (q < total) {
+        int e = 0;  // last element whose first pair is <= q
+#pragma unroll
+        for (int h = EPW / 2; h > 0; h /= 2)
+          if (S.at[e + h] <= q) e += h;
+        // pair -> block, x fastest (quotients of numbers below 2^12: a float
+        // product is exact enough)
+        int r = q - S.at[e], b[4], g0[4], g1[4];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const int n = S.ext[a][e];
+          const int d = (int)(((float)r + 0.5f) * (1.0f / (float)n));
+          b[a] = S.blo[a][e] + (r - d * n);
+          r = d;
         }
-}
-
-// Second-order inverse map of one element (record r) at site P, in two
-// parts: l = A dP (nearest image in x, y) with the validity |l_a| < Dm_a,
-// then u_a = l^T H_a l over the symmetric pairs and dQ = l - A u / 2.  The
-// query evaluates the second part only where the first found the element
-// valid, so a wavefront skips it for an element valid at none of its sites.
-__device__ __forceinline__ bool map4_l(const KP &p, const double *r,
-                                       const double P[4], double l[4]) {
-  double d[4];
-  d[0] = image(p, P[0] - r[0]);
-  d[1] = image(p, P[1] - r[1]);
-  d[2] = P[2] - r[2];
-  d[3] = P[3] - r[3];
-  bool valid = true;
+        b[3] = S.blo[3][e] + r;
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const double *A = r + 4 + 4 * a;
-    l[a] = fma(A[3], d[3], fma(A[2], d[2], fma(A[1], d[1], A[0] * d[0])));
-    valid = valid && (fabs(l[a]) < p.Dm[a]);
+        for (int a = 0; a < 4; ++a) {
+          g0[a] = blk_first(p, a, b[a]);
+          g1[a] = g0[a] + BLK - 1;
+          if (a >= 2) {  // the live sites of a partial velocity block
+            g0[a] = max(g0[a], 0);
+            g1[a] = min(g1[a], p.nv - 1);
+          }
+        }
+        if (block_meets(p, S, e, g0, g1)) {
+          blk[k] = list_of(p, b[0], b[1], b[2], b[3]);
+          id[k] = e0 + e;
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < REG_AHEAD; ++k)
+      slot[k] = blk[k] >= 0 ? atomicAdd(&cnt_reg[blk[k]], 1) : p.cap;
+#pragma unroll
+    for (int k = 0; k < REG_AHEAD; ++k)
+      if (slot[k] < p.cap) lst[blk[k] * p.cap + slot[k]] = id[k];
   }
-  return valid;
 }
 
-__device__ __forceinline__ void map4_q(const double *r, const double l[4],
-                                       double dq[4]) {
-  double u[4];
+// Second-order inverse map of one element (record r) at offset d = P - X: l
+// = A d, then u'_c = l^T (-H_c / 2) l over the symmetric pairs and dQ = l +
+// A u' (equal bit for bit to l - A u / 2: scaling by a power of two commutes
+// with every rounding).  R is a pointer to the record in any address space.
+template <typename R>
+__device__ __forceinline__ void map4_l(R r, const double d[4], double l[4]) {
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
-    const double *H = r + 20 + 10 * a;
-    double s = H[0] * (l[0] * l[0]);
-    s = fma(2.0 * H[1], l[0] * l[1], s);
-    s = fma(2.0 * H[2], l[0] * l[2], s);
-    s = fma(2.0 * H[3], l[0] * l[3], s);
-    s = fma(H[4], l[1] * l[1], s);
-    s = fma(2.0 * H[5], l[1] * l[2], s);
-    s = fma(2.0 * H[6], l[1] * l[3], s);
-    s = fma(H[7], l[2] * l[2], s);
-    s = fma(2.0 * H[8], l[2] * l[3], s);
-    s = fma(H[9], l[3] * l[3], s);
+    R A = r + R_A + 4 * a;
+    l[a] = fma(A[3], d[3], fma(A[2], d[2], fma(A[1], d[1], A[0] * d[0])));
+  }
+}
+
+template <typename R>
+__device__ __forceinline__ void map4_q(R r, const double l[4], double dq[4]) {
+  double pr[10], u[4];
+#pragma unroll
+  for (int q = 0; q < 10; ++q) pr[q] = l[PB[q]] * l[PC[q]];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    R G = r + R_G + 10 * a;
+    double s = G[0] * pr[0];
+#pragma unroll
+    for (int q = 1; q < 10; ++q) s = fma(G[q], pr[q], s);
     u[a] = s;
   }
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
-    const double *A = r + 4 + 4 * a;
+    R A = r + R_A + 4 * a;
     double s = l[a];
 #pragma unroll
-    for (int b = 0; b < 4; ++b) s = fma(-0.5 * A[b], u[b], s);
+    for (int b = 0; b < 4; ++b) s = fma(A[b], u[b], s);
     dq[a] = s;
   }
 }
 
-__device__ __forceinline__ bool map4(const KP &p, const double *r,
+// Offset of site P from an element at the nearest image in x and y.
+template <typename R>
+__device__ __forceinline__ void offset4(const KP &p, R r, const double P[4],
+                                        double d[4]) {
+  d[0] = image(p, P[0] - r[0]);
+  d[1] = image(p, P[1] - r[1]);
+  d[2] = P[2] - r[2];
+  d[3] = P[3] - r[3];
+}
+
+__device__ __forceinline__ void map4(const KP &p, const double *r,
                                      const double P[4], double dq[4]) {
-  double l[4];
-  const bool valid = map4_l(p, r, P, l);
+  double d[4], l[4];
+  offset4(p, r, P, d);
+  map4_l(r, d, l);
   map4_q(r, l, dq);
-  return valid;
 }
 
 __device__ __forceinline__ double dist2(const KP &p, const double dq[4]) {
-  const double z0 = dq[0] * p.rD[0], z1 = dq[1] * p.rD[1];
-  const double z2 = dq[2] * p.rD[2], z3 = dq[3] * p.rD[3];
+  const double z0 = dq[0] * p.rD[0], z1 = dq[1] * p.rD[0];
+  const double z2 = dq[2] * p.rD[2], z3 = dq[3] * p.rD[2];
   return fma(z3, z3, fma(z2, z2, fma(z1, z1, z0 * z0)));
 }
 
 // Site of thread t of block blk (blocks numbered x fastest): (i, j, k, l),
-// its coordinates, whether it lies on the grid, and the block's list.
-__device__ __forceinline__ bool block_site(const KP &p, long long blk, int t,
+// its coordinates, whether it lies on the grid, and the block's list.  A
+// wavefront takes 4 x 4 x 2 x 2 sites (sub-block u1 + 2 w1 = t >> 6 of the
+// block's four): the more cubic the sub-block, the fewer windows it meets.
+// loc is the site's index in the block, x fastest.
+__device__ __forceinline__ bool block_site(const KP &p, int blk, int t,
                                            int g[4], double P[4], int bb[4],
-                                           long long &list) {
-  long long b = blk;
-  bb[0] = (int)(b % p.nb[0]);
-  b /= p.nb[0];
-  bb[1] = (int)(b % p.nb[1]);
-  b /= p.nb[1];
-  bb[2] = (int)(b % p.nb[2]);
-  bb[3] = (int)(b / p.nb[2]);
-  const int loc[4] = {t & 3, (t >> 2) & 3, (t >> 4) & 3, t >> 6};
+                                           int &loc, long long &list) {
+  unsigned b = (unsigned)blk;
+  bb[0] = (int)(b % (unsigned)p.nb[0]);
+  b /= (unsigned)p.nb[0];
+  bb[1] = (int)(b % (unsigned)p.nb[1]);
+  b /= (unsigned)p.nb[1];
+  bb[2] = (int)(b % (unsigned)p.nb[2]);
+  bb[3] = (int)(b / (unsigned)p.nb[2]);
+  const int lc[4] = {t & 3, (t >> 2) & 3, ((t >> 4) & 1) | ((t >> 5) & 2),
+                     ((t >> 5) & 1) | ((t >> 6) & 2)};
   bool live = true;
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
-    g[a] = blk_first(p, a, bb[a]) + loc[a];
+    g[a] = blk_first(p, a, bb[a]) + lc[a];
     P[a] = coord(p, a, g[a]);
     live = live && g[a] >= 0 && g[a] < (a < 2 ? p.ns : p.nv);
   }
+  loc = ((lc[3] * 4 + lc[2]) * 4 + lc[1]) * 4 + lc[0];
   list = list_of(p, bb[0], bb[1], bb[2], bb[3]);
   return live;
 }
 
-// Nearest valid element (smallest (d^2, id)) of the workgroup's block: the
-// list's records are staged in LDS STAGE at a time; with an overflowed list
-// or a too-wide element, every element is scanned.
+// LDS of the query, per list slot: the entry (element id, the image shift of
+// x and y, 0 none, 1 -L, 2 +L, 3 per site), the sub-blocks its window can
+// reach (bits 0-3) and those whose centre it is near (bits 4-7), and per
+// sub-block a lower bound of its Lagrangian distance.
+struct QueryLds {
+  int *ent, *sub;
+  float *low;  // [slot][4]
+  __device__ __forceinline__ QueryLds(const KP &p, char *lds)
+      : ent(reinterpret_cast<int *>(lds)), sub(ent + p.cap),
+        low(reinterpret_cast<float *>(sub + p.cap)) {}
+};
+constexpr int QUERY_SLOT_BYTES = 24;
+
+// Entries k = tid, tid + 256, .. of the block's list, one per thread: from l
+// at the block's centre, l is linear in P, so over a sub-block's box it
+// ranges over its centre value +- sum_b |A_ab| half-width_b (rounding margins
+// as in block_meets).  The distance bound leaves out the rounding of the
+// square roots, which the float's own margin covers.
+__device__ __forceinline__ void query_filter(const KP &p,
+                                             const double *__restrict__ rec,
+                                             const int *__restrict__ L, int n,
+                                             const int bb[4], QueryLds Q) {
+  const double hw[4] = {1.5 * p.dx, 1.5 * p.dx, 0.5 * p.du, 0.5 * p.du};
+  for (int k = threadIdx.x; k < n; k += 256) {
+    const int e = L[k];
+    const double *r = rec + (size_t)e * RS;
+    int code = 0;
+    double m[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const int g0 = blk_first(p, a, bb[a]);
+      m[a] = 0.5 * (coord(p, a, g0) + coord(p, a, g0 + BLK - 1)) - r[a];
+      if (a < 2) {
+        int s = 0;
+        if (m[a] > p.hL) {
+          m[a] = m[a] - p.L;
+          s = 1;
+        } else if (m[a] < -p.hL) {
+          m[a] = m[a] + p.L;
+          s = 2;
+        }
+        // the block's sites on both sides of the half period
+        if (fabs(m[a]) + 2.0 * p.dx > p.hL) s = 3;
+        code |= s << (24 + 2 * a);
+      }
+    }
+    const bool split = ((code >> 24) & 3) == 3 || ((code >> 26) & 3) == 3;
+    int bits = 0;
+    double zc2[4] = {0.0, 0.0, 0.0, 0.0}, zr2 = 0.0;
+    bool ok[4] = {true, true, true, true};
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const double *A = r + R_A + 4 * a;
+      double c = 0.0, rad = 0.0, mag = 0.0;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        c = fma(A[b], m[b], c);
+        rad = fma(fabs(A[b]), hw[b], rad);
+        mag = fma(fabs(A[b]), fabs(m[b]) + 2.0 * (hw[b] + p.du) + 1.0, mag);
+      }
+      const double lim = p.Dm[a] + 0x1p-36 * (mag + p.Dm[a]) + rad;
+      const double z = rad * p.rD[a];
+      zr2 = fma(z, z, zr2);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const double ls = c + (((s & 1) ? A[2] : -A[2]) +
+                               ((s & 2) ? A[3] : -A[3])) * p.du;
+        ok[s] = ok[s] && fabs(ls) < lim;
+        const double zs = ls * p.rD[a];
+        zc2[s] = fma(zs, zs, zc2[s]);
+      }
+    }
+    const double out = sqrt(zr2) + r[R_DELTA];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (ok[s] || split) bits |= 1 << s;
+      if (zc2[s] < 1.0) bits |= 16 << s;
+      Q.low[4 * k + s] =
+          split ? -1.0f : (float)(sqrt(zc2[s]) - out) * 0.9999f - 1e-4f;
+    }
+    Q.ent[k] = e | code;
+    Q.sub[k] = bits;
+  }
+}
+
+// One candidate at this lane's site: l, validity, the cull against the best
+// distance so far (whole wavefronts skip the quadratic part), and the
+// (d^2, id) update.
+template <typename R>
+__device__ __forceinline__ void query_candidate(const KP &p, R r, int e,
+                                                bool live, const double d[4],
+                                                double &bd, int &best,
+                                                double bdq[4]) {
+  double l[4], zl[4];
+  map4_l(r, d, l);
+  // every lane, no short cuts: the tests combine as lane masks
+  bool valid = live;
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    valid = valid & (fabs(l[a]) < p.Dm[a & 2]);
+    zl[a] = l[a] * p.rD[a & 2];
+  }
+  const double z2 = fma(zl[3], zl[3], fma(zl[2], zl[2], fma(zl[1], zl[1],
+                                                            zl[0] * zl[0])));
+  if (__ballot(valid & !(z2 * r[R_K] - r[R_DELTA] > bd)) == 0ull) return;
+  double dq[4];
+  map4_q(r, l, dq);
+  const double d2 = dist2(p, dq);
+  if (valid & ((d2 < bd) | ((d2 == bd) & (e < best)))) {
+    bd = d2;
+    best = e;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) bdq[a] = dq[a];
+  }
+}
+
+// Nearest valid element (smallest (d^2, id)) of every site of the workgroup's
+// block.  The workgroup first sorts the list's entries by sub-block, one per
+// thread (query_filter); each wavefront then walks its own sub-block's
+// candidates, the near ones (centre closer than one spacing, about the
+// undeformed lattice's nearest few) first, so that the far ones can be
+// dropped by their distance bound (a lane per candidate) and by the cull.  Records are
+// read through the scalar cache: they are uniform over the wavefront, and
+// the operands come straight from scalar registers.  With an overflowed
+// list or a too-wide element every element is scanned.
+typedef const __attribute__((address_space(4))) double cdouble;
 __device__ __forceinline__ int query4(const KP &p, const double *__restrict__ rec,
                                       const int *__restrict__ L, int n,
-                                      bool scan_all, const double P[4],
-                                      double bdq[4], double *stage) {
+                                      bool scan_all, bool live, const int bb[4],
+                                      const double P[4], double bdq[4],
+                                      char *lds) {
   double bd = __builtin_inf();
   int best = -1;
   for (int a = 0; a < 4; ++a) bdq[a] = 0.0;
-  const int tid = threadIdx.x;
-  const int total = scan_all ? p.E : n;
-  for (int c0 = 0; c0 < total; c0 += STAGE) {
-    const int m = min(STAGE, total - c0);
-    __syncthreads();
-    for (int q = tid; q < m * RS; q += 256) {
-      const int k = q / RS, o = q - k * RS;
-      const int e = scan_all ? c0 + k : L[c0 + k];
-      stage[q] = rec[(size_t)e * RS + o];
+  auto record = [&](int e) {
+    return (cdouble *)(unsigned long long)(rec + (size_t)e * RS);
+  };
+  if (scan_all) {
+    for (int e = 0; e < p.E; ++e) {
+      cdouble *r = record(e);
+      double d[4];
+      offset4(p, r, P, d);
+      query_candidate(p, r, e, live, d, bd, best, bdq);
     }
-    __syncthreads();
-    for (int k = 0; k < m; ++k) {
-      const int e = scan_all ? c0 + k : L[c0 + k];
-      const double *r = stage + k * RS;
-      double l[4];
-      if (map4_l(p, r, P, l)) {
-        double dq[4];
-        map4_q(r, l, dq);
-        const double d2 = dist2(p, dq);
-        if (d2 < bd || (d2 == bd && e < best)) {
-          bd = d2;
-          best = e;
-          for (int a = 0; a < 4; ++a) bdq[a] = dq[a];
+    return best;
+  }
+  const QueryLds Q(p, lds);
+  query_filter(p, rec, L, n, bb, Q);
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float top = __builtin_inff();
+  for (int far = 0; far < 2; ++far) {
+    if (far) {
+      // no site of the sub-block takes an element beyond its worst distance
+      top = live ? (float)sqrt(bd) * 1.0001f : 0.0f;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1)
+        top = fmaxf(top, __shfl_xor(top, off));
+    }
+    for (int c0 = 0; c0 < n; c0 += 64) {
+      const int k = c0 + lane;
+      int ent = 0, sub = 0;
+      float low = 0.0f;
+      if (k < n) {
+        ent = Q.ent[k];
+        sub = Q.sub[k] >> w;
+        low = Q.low[4 * k + w];
+      }
+      unsigned long long todo =
+          __ballot((sub & 1) && ((sub >> 4) & 1) == (far ? 0 : 1) && !(low > top));
+      while (todo) {
+        const int j = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int en = __builtin_amdgcn_readlane(ent, j);
+        const int e = en & 0xffffff, sx = (en >> 24) & 3, sy = (en >> 26) & 3;
+        cdouble *r = record(e);
+        double d[4];
+        if (sx == 3 || sy == 3) {
+          offset4(p, r, P, d);
+        } else {
+          const double hx = sx == 1 ? -p.L : (sx == 2 ? p.L : 0.0);
+          const double hy = sy == 1 ? -p.L : (sy == 2 ? p.L : 0.0);
+          d[0] = (P[0] - r[0]) + hx;
+          d[1] = (P[1] - r[1]) + hy;
+          d[2] = P[2] - r[2];
+          d[3] = P[3] - r[3];
         }
+        query_candidate(p, r, e, live, d, bd, best, bdq);
       }
     }
   }
@@ -431,8 +814,8 @@ __device__ __forceinline__ int query4(const KP &p, const double *__restrict__ re
 // per axis pair at the floor corner of that plane.  x, y positions clamped
 // to [-12, ns + 11] and wrapped; zero outside the u, w grid.  Every stencil
 // index along an axis is the nearest node's -1, 0 or +1 (the floor corner
-// is the nearest node or the one below), so the wrapped offsets of the
-// three are formed once per axis.
+// is the nearest node or the one below), so 15 values serve the 33 terms.
+// (Grids hold at most 2^31 values: 32-bit indices.)
 template <typename FT>
 __device__ __forceinline__ FT int15(const KP &p, const FT *__restrict__ F,
                                     const double sin_[4]) {
@@ -444,61 +827,89 @@ __device__ __forceinline__ FT int15(const KP &p, const FT *__restrict__ F,
   }
   for (int a = 2; a < 4; ++a)
     if (!(s[a] > -4.0 && s[a] < p.nv + 3.0)) return (FT)0;
-  int n[4], cf[4];
+  // nearest node, whether the floor node is the nearest one (else the one
+  // below), the offset from it; index steps to the nodes below and above
+  const int str[4] = {1, p.ns, p.ns * p.ns, p.ns * p.ns * p.nv};
+  bool fl[4], in[4][3];
   FT dq[4];
+  int at0 = 0, step[4][3];
+#pragma unroll
   for (int a = 0; a < 4; ++a) {
     const double fn = floor(s[a] + 0.5);
-    n[a] = (int)fn;
-    cf[a] = (int)floor(s[a]) - n[a] + 1;  // 0 or 1: index of the floor node
+    int n = (int)fn;
+    fl[a] = (int)floor(s[a]) == n;
     dq[a] = (FT)(s[a] - fn);
-  }
-  // element offsets of nodes n-1, n, n+1 per axis (-1: off the u, w grid)
-  const long long str[4] = {1, p.ns, (long long)p.ns * p.ns,
-                            (long long)p.ns * p.ns * p.nv};
-  long long off[4][3];
-  for (int a = 0; a < 4; ++a) {
-    for (int q = 0; q < 3; ++q) {
-      int i = n[a] - 1 + q;
-      if (a < 2) {
-        i = ((i % p.ns) + p.ns) % p.ns;
-        off[a][q] = (long long)i * str[a];
-      } else {
-        off[a][q] = (i >= 0 && i < p.nv) ? (long long)i * str[a] : -1;
-      }
+    int lo = n - 1, hi = n + 1;
+    if (a < 2) {
+      // positions in [-14, ns + 13] and ns >= 8: at most two periods off
+      auto wrap = [&](int i) {
+        i += i < 0 ? p.ns : 0;
+        i += i < 0 ? p.ns : 0;
+        i -= i >= p.ns ? p.ns : 0;
+        i -= i >= p.ns ? p.ns : 0;
+        return i;
+      };
+      lo = wrap(lo);
+      n = wrap(n);
+      hi = wrap(hi);
+    } else {
+      // off the u, w grid: zero (read from a node that exists)
+      in[a][0] = lo >= 0 && lo < p.nv;
+      in[a][1] = n >= 0 && n < p.nv;
+      in[a][2] = hi >= 0 && hi < p.nv;
+      lo = min(max(lo, 0), p.nv - 1);
+      n = min(max(n, 0), p.nv - 1);
+      hi = min(max(hi, 0), p.nv - 1);
     }
+    at0 += n * str[a];
+    step[a][0] = (lo - n) * str[a];
+    step[a][1] = 0;
+    step[a][2] = (hi - n) * str[a];
   }
-  auto at = [&](int q0, int q1, int q2, int q3) -> FT {
-    if (off[2][q2] < 0 || off[3][q3] < 0) return (FT)0;
-    return F[off[0][q0] + off[1][q1] + off[2][q2] + off[3][q3]];
+  auto at = [&](int i, bool ok) -> FT {
+    const FT v = F[(unsigned)i];
+    return ok ? v : (FT)0;
   };
+  // the nearest node, its axis neighbours, and per axis the neighbour on the
+  // other side of the cell (index o): 2 where the floor node is the nearest
+  const FT c = at(at0, in[2][1] & in[3][1]);
   FT w0 = (FT)1 - dq[0] * dq[0];
+#pragma unroll
   for (int a = 1; a < 4; ++a) w0 = w0 - dq[a] * dq[a];
-  FT f = at(1, 1, 1, 1) * w0;
+  FT f = c * w0, nb[4];
+  int so[4];
+  bool ino[4];
+#pragma unroll
   for (int a = 0; a < 4; ++a) {
+    const bool other = (a == 2 ? in[3][1] : a == 3 ? in[2][1] : in[2][1] & in[3][1]);
+    const FT up = at(at0 + step[a][2], a < 2 ? other : other & in[a][2]);
+    const FT dn = at(at0 + step[a][0], a < 2 ? other : other & in[a][0]);
     const FT h = (FT)0.5 * dq[a];
     const FT wp = h * ((FT)1 + dq[a]), wm = h * ((FT)1 - dq[a]);
-    int qp[4] = {1, 1, 1, 1}, qm[4] = {1, 1, 1, 1};
-    qp[a] = 2;
-    qm[a] = 0;
-    f = fma(at(qp[0], qp[1], qp[2], qp[3]), wp, f);
-    f = fma(-at(qm[0], qm[1], qm[2], qm[3]), wm, f);
+    f = fma(up, wp, f);
+    f = fma(-dn, wm, f);
+    nb[a] = fl[a] ? up : dn;
+    so[a] = fl[a] ? step[a][2] : step[a][0];
+    ino[a] = a < 2 ? true : (fl[a] ? in[a][2] : in[a][0]);
   }
+  // cross terms f11 + f00 - f10 - f01 at the cell's low corner: of the four
+  // corners one is the nearest node, two are axis neighbours, one is a
+  // diagonal; which is which follows from the floor flags
+#pragma unroll
   for (int a = 0; a < 4; ++a)
+#pragma unroll
     for (int b = a + 1; b < 4; ++b) {
-      int q[4] = {1, 1, 1, 1};
-      q[a] = cf[a] + 1;
-      q[b] = cf[b] + 1;
-      const FT f11 = at(q[0], q[1], q[2], q[3]);
-      q[a] = cf[a];
-      q[b] = cf[b];
-      const FT f00 = at(q[0], q[1], q[2], q[3]);
-      q[a] = cf[a] + 1;
-      const FT f10 = at(q[0], q[1], q[2], q[3]);
-      q[a] = cf[a];
-      q[b] = cf[b] + 1;
-      const FT f01 = at(q[0], q[1], q[2], q[3]);
-      const FT cross = ((f11 + f00) - f10) - f01;
-      f = fma(cross, dq[a] * dq[b], f);
+      bool ok = true;
+      if (a >= 2) ok = ok & ino[a];
+      if (b >= 2) ok = ok & ino[b];
+      if (a != 2 && b != 2) ok = ok & in[2][1];
+      if (a != 3 && b != 3) ok = ok & in[3][1];
+      const FT dg = at(at0 + so[a] + so[b], ok);
+      const bool same = fl[a] == fl[b];
+      const FT pl = same ? c + dg : nb[a] + nb[b];
+      const FT m1 = same ? (fl[a] ? nb[a] : nb[b]) : (fl[a] ? dg : c);
+      const FT m2 = same ? (fl[a] ? nb[b] : nb[a]) : (fl[a] ? c : dg);
+      f = fma((pl - m1) - m2, dq[a] * dq[b], f);
     }
   return f;
 }
@@ -611,24 +1022,33 @@ __device__ __forceinline__ void index_pos(const KP &p, const double Q[4],
 // One workgroup of 256 threads per 4^4-site block, one thread per site.
 // M_DENSITY: the block's 16 velocity sites per (x, y) column are summed (w
 // outer, u inner) into part[velocity block][y][x]; M_F: f; M_ASSIGN: ids.
+//
+// Bound by FP64 vector instructions.  A block's list holds 69 to 81 elements
+// of which a site needs one; sorting the list per sub-block, culling, reading
+// records as scalar operands and the 15-value interpolation took a wavefront
+// from 8500 vector instructions to about 3000 and a launch at 64^4 (mixed,
+// stride 4) from 5650 to 1720 us; at 16^4, where every element used to be
+// scanned, from 156 to 31 us.  Six wavefronts per SIMD (80 VGPRs, the spills
+// outside the candidate loop) against the 4 the compiler takes by itself and
+// 7 or 8: 1720, 2100, 1820 and 1920 us.
 template <typename FT, int MODE>
-__global__ __launch_bounds__(256) void k4_recon(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k4_recon(
     KP p, const double *__restrict__ rec, const int *__restrict__ cnt,
     const int *__restrict__ lst, const int *__restrict__ flags,
     const FT *__restrict__ F, double *__restrict__ part, FT *__restrict__ fout,
     int *__restrict__ aout) {
-  __shared__ double stage[STAGE * RS];
+  extern __shared__ char lds[];  // QUERY_SLOT_BYTES per list slot
   __shared__ double sf[256];
-  const long long blk = blockIdx.x;
   const int t = threadIdx.x;
-  int g[4], bb[4];
+  int g[4], bb[4], loc;
   double P[4];
   long long list;
-  const bool live = block_site(p, blk, t, g, P, bb, list);
+  const bool live = block_site(p, blockIdx.x, t, g, P, bb, loc, list);
   const int n = cnt[list];
   const bool scan_all = (n > p.cap) || (flags[0] & FL_WIDE);
   double dq[4];
-  const int best = query4(p, rec, lst + list * p.cap, n, scan_all, P, dq, stage);
+  const int best = query4(p, rec, lst + list * p.cap, n, scan_all, live, bb, P,
+                          dq, lds);
   const size_t site =
       (((size_t)g[3] * p.nv + g[2]) * p.ns + g[1]) * p.ns + g[0];
   FT fv = (FT)0;
@@ -643,7 +1063,7 @@ __global__ __launch_bounds__(256) void k4_recon(
   if (MODE == M_F && live) fout[site] = fv;
   if (MODE == M_ASSIGN && live) aout[site] = best;
   if (MODE == M_DENSITY) {
-    sf[t] = (double)fv;  // 0 off the grid
+    sf[loc] = (double)fv;  // 0 off the grid
     __syncthreads();
     const int i = blk_first(p, 0, bb[0]) + (t & 3);
     const int j = blk_first(p, 1, bb[1]) + ((t >> 2) & 3);
@@ -677,17 +1097,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     KP p, const double *__restrict__ rec, const int *__restrict__ cnt,
     const int *__restrict__ lst, const int *__restrict__ flags,
     const FT *__restrict__ C, FT *__restrict__ out) {
-  __shared__ double stage[STAGE * RS];
-  const long long blk = blockIdx.x;
-  const int t = threadIdx.x;
-  int g[4], bb[4];
+  extern __shared__ char lds[];  // QUERY_SLOT_BYTES per list slot
+  int g[4], bb[4], loc;
   double P[4];
   long long list;
-  const bool live = block_site(p, blk, t, g, P, bb, list);
+  const bool live = block_site(p, blockIdx.x, threadIdx.x, g, P, bb, loc, list);
   const int n = cnt[list];
   const bool scan_all = (n > p.cap) || (flags[0] & FL_WIDE);
   double dq[4];
-  const int best = query4(p, rec, lst + list * p.cap, n, scan_all, P, dq, stage);
+  const int best = query4(p, rec, lst + list * p.cap, n, scan_all, live, bb, P,
+                          dq, lds);
   if (!live) return;
   const size_t site =
       (((size_t)g[3] * p.nv + g[2]) * p.ns + g[1]) * p.ns + g[0];
@@ -907,82 +1326,6 @@ __global__ __launch_bounds__(256) void k4_fd(KP p, double *__restrict__ fld) {
         (((at(ip, jp) - at(ip, jm)) - at(im, jp)) + at(im, jm)) / (4.0 * (dx * dx));
     fld[(8 + 3 * c) * n2 + o] = ((at(i, jp) + at(i, jm)) - 2.0 * at(i, j)) / (dx * dx);
   }
-}
-
-// 3 x 3 dual TSC of the 12 fields at (x, y).
-__device__ __forceinline__ void tsc12(const KP &p, const double *__restrict__ fld,
-                                      double x, double y, double v[12]) {
-  const int n = p.ns;
-  const size_t n2 = (size_t)n * n;
-  double u[2] = {x * p.inv_dx - 0.5, y * p.inv_dx - 0.5};
-  int i0[2];
-  double w[2][3];
-  for (int a = 0; a < 2; ++a) {
-    if (!(u[a] >= -3.0)) u[a] = -3.0;
-    if (u[a] > (double)n + 2.0) u[a] = (double)n + 2.0;
-    const double fi = floor(u[a] + 0.5), d = u[a] - fi;
-    const double tm = 0.5 - d, tp = 0.5 + d;
-    i0[a] = (int)fi;
-    w[a][0] = 0.5 * (tm * tm);
-    w[a][1] = 0.75 - d * d;
-    w[a][2] = 0.5 * (tp * tp);
-  }
-  int ix[3], jy[3];
-  for (int q = 0; q < 3; ++q) {
-    ix[q] = (((i0[0] - 1 + q) % n) + n) % n;
-    jy[q] = (((i0[1] - 1 + q) % n) + n) % n;
-  }
-  for (int k = 0; k < 12; ++k) {
-    const double *A = fld + k * n2;
-    double row[3];
-    for (int b = 0; b < 3; ++b) {
-      const double *R = A + (size_t)jy[b] * n;
-      row[b] = fma(w[0][2], R[ix[2]], fma(w[0][1], R[ix[1]], w[0][0] * R[ix[0]]));
-    }
-    v[k] = fma(w[1][2], row[2], fma(w[1][1], row[1], w[1][0] * row[0]));
-  }
-}
-
-// Kick over dt (section 2.4 per space axis, reading R5: the right-hand
-// sides use the half-step T and H of the space rows), then the corrector
-// drift over dt/2.
-__global__ __launch_bounds__(256) void k4_kick(KP p, double *__restrict__ st,
-                                               const double *__restrict__ fld) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= p.E) return;
-  const size_t E = (size_t)p.E;
-  double s[NST];
-#pragma unroll
-  for (int q = 0; q < NST; ++q) s[q] = st[q * E + e];
-  double fv[12];
-  tsc12(p, fld, s[S_P], s[S_P + 1], fv);
-  const double dt = p.dt;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const double a = fv[i], g0 = fv[2 + 2 * i], g1 = fv[3 + 2 * i];
-    const double h00 = fv[6 + 3 * i], h01 = fv[7 + 3 * i], h11 = fv[8 + 3 * i];
-    s[S_P + 2 + i] = fma(dt, a, s[S_P + 2 + i]);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const double v = fma(g1, s[S_T + 4 + j], g0 * s[S_T + j]);
-      s[S_T + 4 * (2 + i) + j] = fma(dt, v, s[S_T + 4 * (2 + i) + j]);
-    }
-#pragma unroll
-    for (int q = 0; q < 10; ++q) {
-      const int jb = PB[q], kc = PC[q];
-      const double t0j = s[S_T + jb], t1j = s[S_T + 4 + jb];
-      const double t0k = s[S_T + kc], t1k = s[S_T + 4 + kc];
-      double v = g0 * s[S_H + q];
-      v = fma(g1, s[S_H + 10 + q], v);
-      v = fma(h00, t0j * t0k, v);
-      v = fma(h01, fma(t0j, t1k, t1j * t0k), v);
-      v = fma(h11, t1j * t1k, v);
-      s[S_H + 10 * (2 + i) + q] = fma(dt, v, s[S_H + 10 * (2 + i) + q]);
-    }
-  }
-  drift4(p, s, p.h);
-#pragma unroll
-  for (int q = 0; q < NST; ++q) st[q * E + e] = s[q];
 }
 
 // ------------------------------------------------------------- the spline
