@@ -20,8 +20,8 @@ namespace {
 thread_local std::string g_err4;
 
 struct Layout {
-  size_t F, C, fs, st, rec, cnt, lst, flags, part, rho, re, im, ar, ai, tr, ti,
-      fld, tw, tabs, tabv, dpart, dout, total;
+  size_t F, C, fs, st, rec, cnt, lst, flags, part, rho, re, im, tr, ti, fld, tw,
+      tabs, tabv, dpart, dout, total;
   long long nb, nl;  // query blocks, lists
 };
 
@@ -111,8 +111,6 @@ Layout make_layout(const vp4_params *p, const KP &k) {
   L.rho = take(n2 * 8);
   L.re = take(n2 * 8);
   L.im = take(n2 * 8);
-  L.ar = take(2 * n2 * 8);
-  L.ai = take(2 * n2 * 8);
   L.tr = take(2 * n2 * 8);
   L.ti = take(2 * n2 * 8);
   L.fld = take(12 * n2 * 8);
@@ -238,27 +236,22 @@ int recon(vp4_ctx *c, void *fout, int *aout) {
                     : recon_t<double, MODE>(c, fout, aout);
 }
 
-// Force fields from a density: DFT along x, along y with the spectra of
-// a_x and a_y, the inverse transforms, then the finite differences.
-int field_from(vp4_ctx *c, const double *rho) {
+// Force fields from a density (given, or summed from the partials into rho):
+// transform along x, along y and back with the spectra of a_x and a_y, back
+// along x with the finite differences.
+int field_from(vp4_ctx *c, const double *part, double *rho) {
   Prof ps(c, PK_FIELD);
   const KP &k = c->k;
-  const long long n2 = (long long)k.ns * k.ns;
   const double *tw = c->at<double>(c->L.tw);
   double *re = c->at<double>(c->L.re), *im = c->at<double>(c->L.im);
-  double *ar = c->at<double>(c->L.ar), *ai = c->at<double>(c->L.ai);
   double *tr = c->at<double>(c->L.tr), *ti = c->at<double>(c->L.ti);
-  double *fld = c->at<double>(c->L.fld);
-  hipLaunchKernelGGL(k4_dft_x, dim3(grid_for(n2, 256)), dim3(256), 0, c->stream,
-                     k, rho, tw, re, im);
-  hipLaunchKernelGGL(k4_dft_y_spec, dim3(grid_for(n2, 256)), dim3(256), 0,
-                     c->stream, k, re, im, tw, ar, ai);
-  hipLaunchKernelGGL(k4_idft_y, dim3(grid_for(2 * n2, 256)), dim3(256), 0,
-                     c->stream, k, ar, ai, tw, tr, ti);
-  hipLaunchKernelGGL(k4_idft_x, dim3(grid_for(2 * n2, 256)), dim3(256), 0,
-                     c->stream, k, tr, ti, tw, fld);
-  hipLaunchKernelGGL(k4_fd, dim3(grid_for(n2, 256)), dim3(256), 0, c->stream,
-                     k, fld);
+  const unsigned row = k.ns * sizeof(double);
+  hipLaunchKernelGGL(k4_rho_dft_x, dim3(k.ns), dim3(FT_WG), 3 * row, c->stream,
+                     k, part, rho, tw, re, im);
+  hipLaunchKernelGGL(k4_spectrum_y, dim3(k.ns), dim3(FT_WG), 8 * row,
+                     c->stream, k, re, im, tw, tr, ti);
+  hipLaunchKernelGGL(k4_force_x, dim3(k.ns), dim3(FT_WG), 8 * row, c->stream,
+                     k, tr, ti, tw, c->at<double>(c->L.fld));
   VP4_CHECK(c, "k4 field");
   return VP4_OK;
 }
@@ -266,12 +259,8 @@ int field_from(vp4_ctx *c, const double *rho) {
 int density_field(vp4_ctx *c, double *rho_out) {
   int rc;
   if ((rc = recon<M_DENSITY>(c, nullptr, nullptr))) return rc;
-  double *rho = rho_out ? rho_out : c->at<double>(c->L.rho);
-  hipLaunchKernelGGL(k4_rho, dim3(grid_for((long long)c->k.ns * c->k.ns, 256)),
-                     dim3(256), 0, c->stream, c->k, c->at<double>(c->L.part),
-                     rho);
-  VP4_CHECK(c, "k4_rho");
-  return field_from(c, rho);
+  return field_from(c, c->at<double>(c->L.part),
+                    rho_out ? rho_out : c->at<double>(c->L.rho));
 }
 
 template <typename FT>
@@ -280,10 +269,11 @@ int fit_t(vp4_ctx *c) {
   const KP &k = c->k;
   const size_t N4 = (size_t)k.ns * k.ns * k.nv * k.nv;
   FT *C = c->at<FT>(c->L.C);
-  hipError_t e = hipMemcpyAsync(C, c->at<FT>(c->L.F), N4 * sizeof(FT),
-                                hipMemcpyDeviceToDevice, c->stream);
-  if (e != hipSuccess) return dev_fail(c, e, "fit copy");
-  for (int ax = 0; ax < 4; ++ax) {
+  const int nl = fitx_lines<FT>(k.ns);
+  hipLaunchKernelGGL((k4_fit_x<FT>), dim3(grid_for((long long)(N4 / k.ns), nl)),
+                     dim3(256), nl * (k.ns + 1) * (int)sizeof(FT), c->stream, k,
+                     c->at<FT>(c->L.F), C, c->at<FT>(c->L.tabs));
+  for (int ax = 1; ax < 4; ++ax) {
     const int n = ax < 2 ? k.ns : k.nv;
     const FT *tab = ax < 2 ? c->at<FT>(c->L.tabs) : c->at<FT>(c->L.tabv);
     hipLaunchKernelGGL((k4_fit<FT>), dim3(grid_for((long long)(N4 / n), 256)),
@@ -543,7 +533,8 @@ int vp4_density(vp4_ctx *c, double *rho) {
 int vp4_field(vp4_ctx *c, const double *rho, double *ax, double *ay) {
   if (!c || !rho || !ax || !ay) return VP4_EINVAL;
   int rc;
-  if ((rc = field_from(c, rho))) return rc;
+  // without partials the density is only read
+  if ((rc = field_from(c, nullptr, const_cast<double *>(rho)))) return rc;
   const size_t n2 = (size_t)c->k.ns * c->k.ns * sizeof(double);
   hipError_t e = hipMemcpyAsync(ax, c->at<double>(c->L.fld), n2,
                                 hipMemcpyDeviceToDevice, c->stream);

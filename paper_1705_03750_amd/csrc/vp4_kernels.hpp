@@ -21,7 +21,7 @@
 //            first and last block of an axis may be partial, and on x and y
 //            they are the two halves of the seam block, which share a list.
 //   part     density partials [velocity blocks][ns^2] (one row of partial
-//            sums per velocity block); rho [ns^2]; spectra and the 12 force
+//            sums per velocity block); rho [ns^2]; transforms and the 12 force
 //            fields (a_x, a_y, grad a, Hessian of a) [12][ns^2].
 #pragma once
 
@@ -1182,178 +1182,204 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 // ------------------------------------------------------------- the field
 
-// rho(i, j) = du dw sum over velocity blocks (in order) of the partials.
-__global__ __launch_bounds__(256) void k4_rho(KP p, const double *__restrict__ part,
-                                              double *__restrict__ rho) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n2 = p.ns * p.ns;
-  if (q >= n2) return;
-  const int nvb = p.nb[2] * p.nb[3];
-  double s = 0.0;
-  for (int v = 0; v < nvb; ++v) s += part[(size_t)v * n2 + q];
-  rho[q] = (p.du * p.du) * s;
+// The discrete Fourier solution of Poisson's equation on the periodic square
+// in three launches of one workgroup per row or column, each holding what its
+// transforms read in LDS (the sums in index order; tw = cos, sin of 2 pi m /
+// ns, the index p i mod ns formed by steps of p).  As six launches of one
+// thread per output, the transforms reading global memory with a 64-bit
+// remainder per term and k4_rho walking its 289 partials on 16 workgroups,
+// the field took 164 us per step at 64^2 (rho 79, x 13, y 26, inverse 26 +
+// 14, differences 5); as three, 32 us (16 + 8 + 8).  Bound by launches and the serial sums.
+constexpr int FT_WG = 256;
+
+// cos, sin of 2 pi m / n into LDS.
+__device__ __forceinline__ void load_tw(const double *__restrict__ tw, int n,
+                                        double *cs) {
+  for (int i = threadIdx.x; i < 2 * n; i += FT_WG) cs[i] = tw[i];
 }
 
-// Discrete Fourier transform of Poisson's equation on the periodic square
-// (the sums in index order; tw = cos, sin of 2 pi m / ns).  Forward along
-// x: R1[j][p] = sum_i rho[j][i] e^{-2 pi i p i / ns}.
-__global__ __launch_bounds__(256) void k4_dft_x(KP p, const double *__restrict__ rho,
-                                                const double *__restrict__ tw,
-                                                double *__restrict__ re,
-                                                double *__restrict__ im) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = p.ns;
-  if (q >= n * n) return;
-  const int j = q / n, pf = q - j * n;
-  const double *cs = tw, *sn = tw + n;
-  double sr = 0.0, si = 0.0;
-  for (int i = 0; i < n; ++i) {
-    const int m = (int)(((long long)pf * i) % n);
-    const double v = rho[(size_t)j * n + i];
-    sr = fma(v, cs[m], sr);
-    si = fma(-v, sn[m], si);
+// Row j = blockIdx.x: rho(i, j) = du dw sum over velocity blocks (in order)
+// of the partials (part != null, rho written) or rho as given, then R1[j][p]
+// = sum_i rho[j][i] e^{-2 pi i p i / ns}.  The partials are requested 32
+// ahead of their additions.
+__global__ __launch_bounds__(FT_WG) void k4_rho_dft_x(
+    KP p, const double *__restrict__ part, double *__restrict__ rho,
+    const double *__restrict__ tw, double *__restrict__ re,
+    double *__restrict__ im) {
+  extern __shared__ double ft[];  // 3 ns doubles
+  const int n = p.ns, j = blockIdx.x;
+  double *row = ft, *cs = ft + n, *sn = cs + n;
+  load_tw(tw, n, cs);
+  const size_t n2 = (size_t)n * n;
+  for (int i = threadIdx.x; i < n; i += FT_WG) {
+    const size_t q = (size_t)j * n + i;
+    if (part) {
+      const int nvb = p.nb[2] * p.nb[3];
+      double s = 0.0;
+      for (int v0 = 0; v0 < nvb; v0 += 32) {
+        double x[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u)
+          x[u] = v0 + u < nvb ? part[(size_t)(v0 + u) * n2 + q] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 32; ++u)
+          if (v0 + u < nvb) s += x[u];
+      }
+      row[i] = (p.du * p.du) * s;
+      rho[q] = row[i];
+    } else {
+      row[i] = rho[q];
+    }
   }
-  re[q] = sr;
-  im[q] = si;
+  __syncthreads();
+  for (int pf = threadIdx.x; pf < n; pf += FT_WG) {
+    double sr = 0.0, si = 0.0;
+    int m = 0;
+    for (int i = 0; i < n; ++i) {
+      const double v = row[i];
+      sr = fma(v, cs[m], sr);
+      si = fma(-v, sn[m], si);
+      m += pf;
+      m -= m >= n ? n : 0;
+    }
+    re[(size_t)j * n + pf] = sr;
+    im[(size_t)j * n + pf] = si;
+  }
 }
 
-// Forward along y: R2[q][p] = sum_j R1[j][p] e^{-2 pi i q j / ns}; then the
-// spectra of a_x and a_y: phi^ = -2 G rho^ / |k|^2, a^ = -i k phi^ (k = 0
-// and the Nyquist derivative zero).  ar/ai hold [2][ns^2].
-__global__ __launch_bounds__(256) void k4_dft_y_spec(
+// Column pf = blockIdx.x: R2[q][pf] = sum_j R1[j][pf] e^{-2 pi i q j / ns};
+// the spectra of a_x and a_y, phi^ = -2 G rho^ / |k|^2, a^ = -i k phi^ (k = 0
+// and the Nyquist derivative zero); back along y, T[c][j][pf] = sum_q
+// a^[c][q][pf] e^{+2 pi i q j / ns}.  tr/ti hold [2][ns^2].
+__global__ __launch_bounds__(FT_WG) void k4_spectrum_y(
     KP p, const double *__restrict__ re, const double *__restrict__ im,
-    const double *__restrict__ tw, double *__restrict__ ar,
-    double *__restrict__ ai) {
-  const int o = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = p.ns;
-  if (o >= n * n) return;
-  const int qy = o / n, pf = o - qy * n;
-  const double *cs = tw, *sn = tw + n;
-  double sr = 0.0, si = 0.0;
-  for (int j = 0; j < n; ++j) {
-    const int m = (int)(((long long)qy * j) % n);
-    const double a = re[(size_t)j * n + pf], b = im[(size_t)j * n + pf];
-    sr = fma(a, cs[m], fma(b, sn[m], sr));
-    si = fma(b, cs[m], fma(-a, sn[m], si));
+    const double *__restrict__ tw, double *__restrict__ tr,
+    double *__restrict__ ti) {
+  extern __shared__ double ft[];  // 8 ns doubles
+  const int n = p.ns, pf = blockIdx.x;
+  double *cs = ft, *sn = cs + n, *rr = sn + n, *ri = rr + n, *ar = ri + n,
+         *ai = ar + 2 * n;
+  load_tw(tw, n, cs);
+  for (int j = threadIdx.x; j < n; j += FT_WG) {
+    rr[j] = re[(size_t)j * n + pf];
+    ri[j] = im[(size_t)j * n + pf];
   }
+  __syncthreads();
   const double twopi = 6.283185307179586476925286766559;
   const int half = (n % 2 == 0) ? n / 2 - 1 : n / 2;
-  const int pp = (pf <= half) ? pf : pf - n, qq = (qy <= half) ? qy : qy - n;
-  const double kx = twopi * (double)pp / p.L, ky = twopi * (double)qq / p.L;
-  const double k2 = kx * kx + ky * ky;
-  const size_t n2 = (size_t)n * n;
-  for (int comp = 0; comp < 2; ++comp) {
-    if (pf == 0 && qy == 0) {
-      ar[comp * n2 + o] = 0.0;
-      ai[comp * n2 + o] = 0.0;
-      continue;
+  for (int qy = threadIdx.x; qy < n; qy += FT_WG) {
+    double sr = 0.0, si = 0.0;
+    int m = 0;
+    for (int j = 0; j < n; ++j) {
+      const double a = rr[j], b = ri[j];
+      sr = fma(a, cs[m], fma(b, sn[m], sr));
+      si = fma(b, cs[m], fma(-a, sn[m], si));
+      m += qy;
+      m -= m >= n ? n : 0;
     }
-    double kd = comp == 0 ? kx : ky;
-    if ((comp == 0 ? pf : qy) * 2 == n) kd = 0.0;
+    const int pp = (pf <= half) ? pf : pf - n, qq = (qy <= half) ? qy : qy - n;
+    const double kx = twopi * (double)pp / p.L, ky = twopi * (double)qq / p.L;
+    const double k2 = kx * kx + ky * ky;
     const double gk = (-2.0 * p.G) / k2;
     const double pr = gk * sr, pi = gk * si;
-    ar[comp * n2 + o] = kd * pi;
-    ai[comp * n2 + o] = -(kd * pr);
+#pragma unroll
+    for (int comp = 0; comp < 2; ++comp) {
+      double kd = comp == 0 ? kx : ky;
+      if ((comp == 0 ? pf : qy) * 2 == n) kd = 0.0;
+      const bool mean = pf == 0 && qy == 0;
+      ar[comp * n + qy] = mean ? 0.0 : kd * pi;
+      ai[comp * n + qy] = mean ? 0.0 : -(kd * pr);
+    }
+  }
+  __syncthreads();
+  const size_t n2 = (size_t)n * n;
+  for (int o = threadIdx.x; o < 2 * n; o += FT_WG) {
+    const int comp = o / n, j = o - comp * n;
+    double sr = 0.0, si = 0.0;
+    int m = 0;
+    for (int qy = 0; qy < n; ++qy) {
+      const double a = ar[comp * n + qy], b = ai[comp * n + qy];
+      sr = fma(a, cs[m], fma(-b, sn[m], sr));
+      si = fma(b, cs[m], fma(a, sn[m], si));
+      m += j;
+      m -= m >= n ? n : 0;
+    }
+    tr[comp * n2 + (size_t)j * n + pf] = sr;
+    ti[comp * n2 + (size_t)j * n + pf] = si;
   }
 }
 
-// Inverse along y for both components: T[c][j][p] = sum_q a^[c][q][p]
-// e^{+2 pi i q j / ns}.
-__global__ __launch_bounds__(256) void k4_idft_y(KP p, const double *__restrict__ ar,
-                                                 const double *__restrict__ ai,
-                                                 const double *__restrict__ tw,
-                                                 double *__restrict__ tr,
-                                                 double *__restrict__ ti) {
-  const int o = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = p.ns;
+// Row j = blockIdx.x: the inverse along x, real part / ns^2, of rows j - 1, j
+// and j + 1 (fields 0, a_x, and 1, a_y, of row j written), then the centred
+// differences of row j: fields 2-5 = d a_x/dx, d a_x/dy, d a_y/dx, d a_y/dy;
+// 6-8 = a_x,xx a_x,xy a_x,yy; 9-11 the same of a_y.
+__global__ __launch_bounds__(FT_WG) void k4_force_x(KP p,
+                                                    const double *__restrict__ tr,
+                                                    const double *__restrict__ ti,
+                                                    const double *__restrict__ tw,
+                                                    double *__restrict__ fld) {
+  extern __shared__ double ft[];  // 8 ns doubles
+  const int n = p.ns, j = blockIdx.x;
   const size_t n2 = (size_t)n * n;
-  if (o >= 2 * n * n) return;
-  const int comp = o / (n * n), r = o - comp * n * n;
-  const int j = r / n, pf = r - j * n;
-  const double *cs = tw, *sn = tw + n;
-  double sr = 0.0, si = 0.0;
-  for (int qy = 0; qy < n; ++qy) {
-    const int m = (int)(((long long)qy * j) % n);
-    const double a = ar[comp * n2 + (size_t)qy * n + pf];
-    const double b = ai[comp * n2 + (size_t)qy * n + pf];
-    sr = fma(a, cs[m], fma(-b, sn[m], sr));
-    si = fma(b, cs[m], fma(a, sn[m], si));
+  double *cs = ft, *sn = cs + n, *a6 = sn + n;  // a6[comp][row j-1, j, j+1][i]
+  load_tw(tw, n, cs);
+  __syncthreads();
+  for (int o = threadIdx.x; o < 6 * n; o += FT_WG) {
+    const int g = o / n, i = o - g * n, comp = g / 3;
+    const int jj = j + g % 3 - 1, jr = jj < 0 ? n - 1 : (jj >= n ? 0 : jj);
+    const double *re = tr + comp * n2 + (size_t)jr * n;
+    const double *im = ti + comp * n2 + (size_t)jr * n;
+    double sr = 0.0;
+    int m = 0;
+#pragma unroll 8
+    for (int pf = 0; pf < n; ++pf) {
+      sr = fma(re[pf], cs[m], fma(-im[pf], sn[m], sr));
+      m += i;
+      m -= m >= n ? n : 0;
+    }
+    a6[o] = sr * (1.0 / ((double)n * (double)n));
   }
-  tr[comp * n2 + r] = sr;
-  ti[comp * n2 + r] = si;
-}
-
-// Inverse along x, real part / ns^2: fields 0 (a_x) and 1 (a_y).
-__global__ __launch_bounds__(256) void k4_idft_x(KP p, const double *__restrict__ tr,
-                                                 const double *__restrict__ ti,
-                                                 const double *__restrict__ tw,
-                                                 double *__restrict__ fld) {
-  const int o = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = p.ns;
-  const size_t n2 = (size_t)n * n;
-  if (o >= 2 * n * n) return;
-  const int comp = o / (n * n), r = o - comp * n * n;
-  const int j = r / n, i = r - j * n;
-  const double *cs = tw, *sn = tw + n;
-  double sr = 0.0;
-  for (int pf = 0; pf < n; ++pf) {
-    const int m = (int)(((long long)pf * i) % n);
-    const double a = tr[comp * n2 + (size_t)j * n + pf];
-    const double b = ti[comp * n2 + (size_t)j * n + pf];
-    sr = fma(a, cs[m], fma(-b, sn[m], sr));
-  }
-  fld[comp * n2 + r] = sr * (1.0 / ((double)n * (double)n));
-}
-
-// Centred differences of a (periodic): fields 2-5 = d a_x/dx, d a_x/dy,
-// d a_y/dx, d a_y/dy; 6-8 = a_x,xx a_x,xy a_x,yy; 9-11 the same of a_y.
-__global__ __launch_bounds__(256) void k4_fd(KP p, double *__restrict__ fld) {
-  const int o = blockIdx.x * blockDim.x + threadIdx.x;
-  const int n = p.ns;
-  const size_t n2 = (size_t)n * n;
-  if (o >= n * n) return;
-  const int j = o / n, i = o - j * n;
-  const int ip = (i + 1) % n, im = (i + n - 1) % n;
-  const int jp = (j + 1) % n, jm = (j + n - 1) % n;
+  __syncthreads();
   const double dx = p.dx;
-  for (int c = 0; c < 2; ++c) {
-    const double *A = fld + c * n2;
-    auto at = [&](int ii, int jj) { return A[(size_t)jj * n + ii]; };
-    fld[(2 + 2 * c) * n2 + o] = (at(ip, j) - at(im, j)) / (2.0 * dx);
-    fld[(3 + 2 * c) * n2 + o] = (at(i, jp) - at(i, jm)) / (2.0 * dx);
-    fld[(6 + 3 * c) * n2 + o] = ((at(ip, j) + at(im, j)) - 2.0 * at(i, j)) / (dx * dx);
-    fld[(7 + 3 * c) * n2 + o] =
-        (((at(ip, jp) - at(ip, jm)) - at(im, jp)) + at(im, jm)) / (4.0 * (dx * dx));
-    fld[(8 + 3 * c) * n2 + o] = ((at(i, jp) + at(i, jm)) - 2.0 * at(i, j)) / (dx * dx);
+  for (int o = threadIdx.x; o < 2 * n; o += FT_WG) {
+    const int c = o / n, i = o - c * n;
+    const int ip = i + 1 < n ? i + 1 : 0, im = i > 0 ? i - 1 : n - 1;
+    const double *A = a6 + c * 3 * n;  // row r of the three at A + r n
+    auto at = [&](int ii, int r) { return A[r * n + ii]; };
+    const size_t q = (size_t)j * n + i;
+    fld[c * n2 + q] = at(i, 1);
+    fld[(2 + 2 * c) * n2 + q] = (at(ip, 1) - at(im, 1)) / (2.0 * dx);
+    fld[(3 + 2 * c) * n2 + q] = (at(i, 2) - at(i, 0)) / (2.0 * dx);
+    fld[(6 + 3 * c) * n2 + q] =
+        ((at(ip, 1) + at(im, 1)) - 2.0 * at(i, 1)) / (dx * dx);
+    fld[(7 + 3 * c) * n2 + q] =
+        (((at(ip, 2) - at(ip, 0)) - at(im, 2)) + at(im, 0)) / (4.0 * (dx * dx));
+    fld[(8 + 3 * c) * n2 + q] =
+        ((at(i, 2) + at(i, 0)) - 2.0 * at(i, 1)) / (dx * dx);
   }
 }
 
 // ------------------------------------------------------------- the spline
 
-// One thread per line along axis `ax` (0 x, 1 y, 2 u, 3 w): the tridiagonal
-// (1, 4, 1) solve with precomputed pivots -- mirror end rows (4, 2) / (2, 4)
-// on u and w, the cyclic system's tridiagonal part plus the Sherman-
-// Morrison correction y - [(y_0 - y_{n-1}/4) / den] z on x and y.
-// tab: cp[n], ri[n] (and z[n], den on the periodic axes).
+// The tridiagonal (1, 4, 1) solves with precomputed pivots, axis by axis (0
+// x, 1 y, 2 u, 3 w): mirror end rows (4, 2) / (2, 4) on u and w, the cyclic
+// system's tridiagonal part plus the Sherman-Morrison correction y - [(y_0 -
+// y_{n-1}/4) / den] z on x and y.  tab: cp[n], ri[n] (and z[n], den on the
+// periodic axes).  fit_line solves one line of n values, `stride` apart, of
+// `in` into x (in place when equal).
 template <typename FT>
-__global__ __launch_bounds__(256) void k4_fit(KP p, FT *__restrict__ C, int ax,
-                                              const FT *__restrict__ tab) {
-  const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long ns = p.ns, nv = p.nv;
-  const long long N4 = ns * ns * nv * nv;
-  const int n = ax < 2 ? p.ns : p.nv;
-  const long long stride = ax == 0 ? 1 : ax == 1 ? ns : ax == 2 ? ns * ns : ns * ns * nv;
-  if (q >= N4 / n) return;
-  const long long low = q % stride, high = q / stride;
-  FT *x = C + high * stride * n + low;
+__device__ __forceinline__ void fit_line(const FT *in, FT *x, int n,
+                                         long long stride, bool per,
+                                         const FT *__restrict__ tab) {
   const FT *cp = tab, *ri = tab + n;
-  const bool per = ax < 2;
   FT acc = (FT)0;
+#pragma unroll 4
   for (int i = 0; i < n; ++i) {
     const FT sub = (!per && i == n - 1) ? (FT)2 : (FT)1;
-    acc = ((FT)6 * x[i * stride] - sub * acc) * ri[i];
+    acc = ((FT)6 * in[i * stride] - sub * acc) * ri[i];
     x[i * stride] = acc;
   }
+#pragma unroll 4
   for (int i = n - 2; i >= 0; --i) {
     acc = x[i * stride] - cp[i] * acc;
     x[i * stride] = acc;
@@ -1363,6 +1389,58 @@ __global__ __launch_bounds__(256) void k4_fit(KP p, FT *__restrict__ C, int ax,
     const FT fact = (x[0] - (FT)0.25 * x[(long long)(n - 1) * stride]) / den;
     for (int i = 0; i < n; ++i) x[i * stride] = x[i * stride] - fact * z[i];
   }
+}
+
+// Axis 0, F -> C: a workgroup brings its lines (contiguous in memory) into
+// LDS with coalesced accesses, a thread solves each there.  With a thread
+// per line on global memory every access touched its own cache line: 1017 us
+// at 64^4 (mixed) after a copy of F; 37 us this way.
+constexpr int FITX_BYTES = 49152;
+template <typename FT>
+__host__ __device__ __forceinline__ int fitx_lines(int n) {
+  const int l = FITX_BYTES / ((n + 1) * (int)sizeof(FT));
+  return l < 64 ? l : 64;
+}
+template <typename FT>
+__global__ __launch_bounds__(256) void k4_fit_x(KP p, const FT *__restrict__ F,
+                                                FT *__restrict__ C,
+                                                const FT *__restrict__ tab) {
+  extern __shared__ char fitx[];  // fitx_lines rows of n + 1 values
+  FT *buf = reinterpret_cast<FT *>(fitx);
+  const int n = p.ns, nl = fitx_lines<FT>(n);
+  const long long lines = (long long)p.ns * p.nv * p.nv;
+  const long long l0 = (long long)blockIdx.x * nl;
+  const int m = (int)min((long long)nl, lines - l0);
+  for (int q = threadIdx.x; q < m * n; q += 256) {
+    const int l = q / n;
+    buf[q + l] = F[l0 * n + q];
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < m) {
+    FT *x = buf + threadIdx.x * (n + 1);
+    fit_line<FT>(x, x, n, 1, true, tab);
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < m * n; q += 256) {
+    const int l = q / n;
+    C[l0 * n + q] = buf[q + l];
+  }
+}
+
+// Axes 1 to 3, in place: one thread per line, neighbouring threads on
+// neighbouring x.
+template <typename FT>
+__global__ __launch_bounds__(256) void k4_fit(KP p, FT *__restrict__ C, int ax,
+                                              const FT *__restrict__ tab) {
+  const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long long ns = p.ns, nv = p.nv;
+  const long long N4 = ns * ns * nv * nv;
+  const int n = ax < 2 ? p.ns : p.nv;
+  const long long stride = ax == 1 ? ns : ax == 2 ? ns * ns : ns * ns * nv;
+  if (q >= N4 / n) return;
+  const long long low = q % stride, high = q / stride;
+  FT *x = C + high * stride * n + low;
+  fit_line<FT>(x, x, n, stride, ax < 2, tab);
 }
 
 // f0 (device doubles) -> F, u and w edge rows zero.
