@@ -963,35 +963,73 @@ __device__ __forceinline__ FT spline4(const KP &p, const FT *__restrict__ C,
     i0[a] = i;
     bspw<FT>(s[a] - (double)i, w[a]);
   }
-  int xi[4], yj[4], uk[4], wl[4];
+  // row offsets along y, u, w (grids hold at most 2^31 values); the first
+  // column of the four along x, and the step to each from it
+  auto wrap = [&](int i) {  // positions in [-14, ns + 13], ns >= 8
+    i += i < 0 ? p.ns : 0;
+    i += i < 0 ? p.ns : 0;
+    i -= i >= p.ns ? p.ns : 0;
+    i -= i >= p.ns ? p.ns : 0;
+    return i;
+  };
+  const int x0 = wrap(i0[0] - 1);
+  unsigned yj[4], uk[4], wl[4];
+#pragma unroll
   for (int q = 0; q < 4; ++q) {
-    xi[q] = (((i0[0] - 1 + q) % p.ns) + p.ns) % p.ns;
-    yj[q] = (((i0[1] - 1 + q) % p.ns) + p.ns) % p.ns;
     int k = i0[2] - 1 + q, l = i0[3] - 1 + q;
     if (k < 0) k = -k;
     if (k > p.nv - 1) k = 2 * (p.nv - 1) - k;
     if (l < 0) l = -l;
     if (l > p.nv - 1) l = 2 * (p.nv - 1) - l;
-    uk[q] = k;
-    wl[q] = l;
+    yj[q] = (unsigned)(wrap(i0[1] - 1 + q) * p.ns);
+    uk[q] = (unsigned)(k * p.ns * p.ns);
+    wl[q] = (unsigned)(l * p.ns * p.ns) * (unsigned)p.nv;
   }
   FT f = (FT)0;
-  for (int l = 0; l < 4; ++l) {
-    FT fu = (FT)0;
-    for (int k = 0; k < 4; ++k) {
-      FT fy = (FT)0;
-      for (int j = 0; j < 4; ++j) {
-        const FT *row =
-            C + (((size_t)wl[l] * p.nv + uk[k]) * p.ns + yj[j]) * p.ns;
-        FT r = w[0][0] * row[xi[0]];
-        r = fma(w[0][1], row[xi[1]], r);
-        r = fma(w[0][2], row[xi[2]], r);
-        r = fma(w[0][3], row[xi[3]], r);
-        fy = (j == 0) ? w[1][0] * r : fma(w[1][j], r, fy);
+  constexpr int AHEAD = 8;
+  // the sum of a row's four terms given its values
+  auto row4 = [&](const FT *c) {
+    FT r = w[0][0] * c[0];
+    r = fma(w[0][1], c[1], r);
+    r = fma(w[0][2], c[2], r);
+    return fma(w[0][3], c[3], r);
+  };
+  auto tensor = [&](auto row) {
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+      FT fu = (FT)0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        FT fy = (FT)0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const FT r = row(wl[l] + uk[k] + yj[j]);
+          fy = (j == 0) ? w[1][0] * r : fma(w[1][j], r, fy);
+        }
+        fu = (k == 0) ? w[2][0] * fy : fma(w[2][k], fy, fu);
+        // at most AHEAD rows in flight: more of them spill
+        if (k % (AHEAD / 4) == AHEAD / 4 - 1) __builtin_amdgcn_sched_barrier(0);
       }
-      fu = (k == 0) ? w[2][0] * fy : fma(w[2][k], fy, fu);
+      f = (l == 0) ? w[3][0] * fu : fma(w[3][l], fu, f);
     }
-    f = (l == 0) ? w[3][0] * fu : fma(w[3][l], fu, f);
+  };
+  // four neighbouring columns are one load (aligned to a value only) unless a
+  // lane's cell lies across the seam
+  if (__ballot(x0 + 3 >= p.ns) == 0ull) {
+    tensor([&](unsigned at) {
+      FT c[4];
+      __builtin_memcpy(c, C + (size_t)(at + (unsigned)x0), sizeof(c));
+      return row4(c);
+    });
+  } else {
+    const int x1 = x0 + 1 < p.ns ? x0 + 1 : x0 + 1 - p.ns;
+    const int x2 = x0 + 2 < p.ns ? x0 + 2 : x0 + 2 - p.ns;
+    const int x3 = x0 + 3 < p.ns ? x0 + 3 : x0 + 3 - p.ns;
+    tensor([&](unsigned at) {
+      const FT *r = C + (size_t)at;
+      const FT c[4] = {r[x0], r[x1], r[x2], r[x3]};
+      return row4(c);
+    });
   }
   if constexpr (sizeof(FT) == 4) f = fmaf(f, INV1296_HI, f * INV1296_LO);
   return f;
@@ -1083,17 +1121,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
 // blend of their Q, tensor spline of F_ini at Q_r; u, w edge rows zero.
 // Writes into out (F_ini when resampling).
 //
-// Four wavefronts per SIMD (at most 128 VGPRs): the per-lane gathers of the
-// neighbours' records need the latency hiding.  The slot offsets and the
-// lattice wrap are selects, not branches that store into small arrays: the
-// branch form, once the register budget made the compiler keep the offsets
-// as one 4-lane vector, was miscompiled at this budget (the control-flow
-// structurizer rebuilt that vector's phi with an undefined incoming value on
-// the path q > 7 of the third axis, so slot 8 re-used slot 7's offsets, the
-// diagonal (0, 0, +1, +1) with zero weight, and the +1 neighbour along the
-// fourth axis dropped out of the blend).
+// Bound by the per-lane gathers: the neighbours' records (480 bytes a slot)
+// and the spline's 256 coefficients.  The four columns of a row as one load
+// and wraps without remainders: 9.30 -> 7.40 ms per launch at 64^4 (mixed,
+// 10 steps), 362 -> 343 us at 32^2 x 24^2 (FP64).  Three wavefronts per SIMD
+// (at most 168 VGPRs): with four (128) the double form spills 100 registers
+// (374 us) and the float form is 1 % slower.
+//
+// The slot offsets and the lattice wrap are selects, not branches that store
+// into small arrays: the branch form, once the register budget made the
+// compiler keep the offsets as one 4-lane vector, was miscompiled (the
+// control-flow structurizer rebuilt that vector's phi with an undefined
+// incoming value on the path q > 7 of the third axis, so slot 8 re-used slot
+// 7's offsets, the diagonal (0, 0, +1, +1) with zero weight, and the +1
+// neighbour along the fourth axis dropped out of the blend).
 template <typename FT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k4_remap(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k4_remap(
     KP p, const double *__restrict__ rec, const int *__restrict__ cnt,
     const int *__restrict__ lst, const int *__restrict__ flags,
     const FT *__restrict__ C, FT *__restrict__ out) {
