@@ -775,10 +775,15 @@ int load_rows(vp_ctx *c, const double *src, int j0, int nrows) {
 // the reconstruction's order, then the largest dv S(i)).
 template <typename FT>
 int clock_init_t(vp_ctx *c) {
-  double *S = c->at<double>(c->L.Ml);  // scratch until the first field
-  hipLaunchKernelGGL((k_colsum_F<FT>), dim3(grid_for(c->k.nx, 256)), dim3(256),
-                     0, c->stream, c->k, c->at<FT>(c->L.F), S);
+  // scratch until the first reconstruction and field
+  double *S = c->at<double>(c->L.Ml), *part = c->at<double>(c->L.part);
+  hipLaunchKernelGGL((k_colsum_F<FT>),
+                     dim3(grid_for(c->k.nx, 256), (unsigned)c->k.ngy),
+                     dim3(256), 0, c->stream, c->k, c->at<FT>(c->L.F), part);
   VP_LAUNCH_CHECK(c, "k_colsum_F");
+  hipLaunchKernelGGL(k_colsum_total, dim3(grid_for(c->k.nx, 64)), dim3(64), 0,
+                     c->stream, c->k, part, S);
+  VP_LAUNCH_CHECK(c, "k_colsum_total");
   hipLaunchKernelGGL(k_clock_init, dim3(1), dim3(1024), 0, c->stream, c->k, S);
   VP_LAUNCH_CHECK(c, "k_clock_init");
   return VP_OK;

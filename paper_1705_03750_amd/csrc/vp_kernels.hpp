@@ -2599,30 +2599,59 @@ __global__ __launch_bounds__(256) void k_load_f0(KP p,
   }
 }
 
-// Variable step, first step (section 2.4): column sums of F_ini, one thread
-// per column, in the fixed order of the reconstruction's density (8-row
-// strips sequential, strips added in order into 64-row groups, groups in
-// increasing order; boundaries on rows congruent to ov), into S[nx].
+// Variable step, first step (section 2.4): column sums of F_ini in the fixed
+// order of the reconstruction's density (8-row strips sequential, strips
+// added in order into 64-row groups, groups in increasing order; boundaries
+// on rows congruent to ov).  k_colsum_F sums row group blockIdx.y of 256
+// columns into part[group][nx], its 64 rows requested ahead of the additions;
+// k_colsum_total adds the groups of every column into S[nx].  One thread per
+// column over all rows waited on a load per row: 276 us at 1020 x 1004
+// (FP64), against 8 + 4 us for the two.
+constexpr int COLSUM_AHEAD = 32;
 template <typename FT>
 __global__ __launch_bounds__(256) void k_colsum_F(KP p,
                                                   const FT *__restrict__ F,
-                                                  double *__restrict__ S) {
+                                                  double *__restrict__ part) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x, g = blockIdx.y;
+  if (i >= p.nx) return;
+  // group 0 ends at row ov when ov > 0 (a partial group), else at row 64
+  const int j0 = max(0, p.ov + 64 * (g - p.obv));
+  const int j1 = min(p.nv, p.ov + 64 * (g - p.obv + 1));
+  const FT *col = F + (long)PV * p.pitch + PX + i;
+  double grp = 0.0, strip = 0.0;
+  for (int jb = j0; jb < j1; jb += COLSUM_AHEAD) {
+    FT v[COLSUM_AHEAD];
+#pragma unroll
+    for (int u = 0; u < COLSUM_AHEAD; ++u)
+      v[u] = (jb + u < j1) ? col[(long)(jb + u) * p.pitch] : (FT)0;
+#pragma unroll
+    for (int u = 0; u < COLSUM_AHEAD; ++u) {
+      const int j = jb + u;
+      if (j < j1) {
+        strip += (double)v[u];
+        if (((j + 1 - p.ov) & 7) == 0 || j == p.nv - 1) {
+          grp += strip;
+          strip = 0.0;
+        }
+      }
+    }
+  }
+  part[(size_t)g * p.nx + i] = grp;
+}
+
+__global__ __launch_bounds__(64) void k_colsum_total(
+    KP p, const double *__restrict__ part, double *__restrict__ S) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= p.nx) return;
-  const FT *col = F + (long)PV * p.pitch + PX + i;
-  double tot = 0.0, grp = 0.0, strip = 0.0;
-  for (int j = 0; j < p.nv; ++j) {
-    strip += (double)col[(long)j * p.pitch];
-    const int r = j + 1 - p.ov;
-    const bool last = (j == p.nv - 1);
-    if ((r & 7) == 0 || last) {
-      grp += strip;
-      strip = 0.0;
-    }
-    if ((r & 63) == 0 || last) {
-      tot += grp;
-      grp = 0.0;
-    }
+  double tot = 0.0;
+  for (int g0 = 0; g0 < p.ngy; g0 += COLSUM_AHEAD) {
+    double v[COLSUM_AHEAD];
+#pragma unroll
+    for (int u = 0; u < COLSUM_AHEAD; ++u)
+      v[u] = (g0 + u < p.ngy) ? part[(size_t)(g0 + u) * p.nx + i] : 0.0;
+#pragma unroll
+    for (int u = 0; u < COLSUM_AHEAD; ++u)
+      if (g0 + u < p.ngy) tot += v[u];
   }
   S[i] = tot;
 }
