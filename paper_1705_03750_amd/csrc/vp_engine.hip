@@ -300,27 +300,34 @@ int launch_elem(vp_ctx *c, int kick, int drift, int predict, int reg,
 // Field from the reconstruction's partials + kick + corrector (+ next
 // predictor) for grids of at most FIELD1_MAX columns: the chunks of the
 // cumulative mass (k_field_chunks, one wavefront per 64 columns), then the
-// element pass that takes its force from them (k_elem_window).
+// element pass that takes its force from them (k_elem_window); on small grids
+// the element pass alone, its workgroups forming the chunks themselves.
 int launch_elem_field(vp_ctx *c, int predict, int reg, int reg_buf,
                       int zero_buf) {
   KP k = c->k;
   k.par ^= 1;  // completes the previous step (see launch_elem)
   ProfScope ps(c, PK_KICK);
-  const int nch = (k.nx + MCHUNK - 1) / MCHUNK;
   const double *part = c->at<double>(c->L.part);
   double *Mc = c->at<double>(c->L.Mc), *ctot = c->at<double>(c->L.ctot),
          *cmax = c->at<double>(c->L.rmx);
-  hipLaunchKernelGGL(k_field_chunks, dim3(nch), dim3(64), 0, c->stream, k,
-                     part, Mc, ctot, cmax);
-  VP_LAUNCH_CHECK(c, "k_field_chunks");
+  const bool own = k.nx <= OWN_MAX_NX && k.nx * k.ngy <= OWN_MAX;
+  if (!own) {
+    const int nch = (k.nx + MCHUNK - 1) / MCHUNK;
+    hipLaunchKernelGGL(k_field_chunks, dim3(nch), dim3(64), 0, c->stream, k,
+                       part, Mc, ctot, cmax);
+    VP_LAUNCH_CHECK(c, "k_field_chunks");
+  }
   double *st = c->at<double>(c->L.st), *rec = c->at<double>(c->L.rec),
          *qm = c->at<double>(c->L.qm);
   int *cz = c->counts(zero_buf), *cr = c->counts(reg_buf);
   const long long nb = c->L.nb;
   int *lst = c->at<int>(c->L.lst), *flags = c->at<int>(c->L.flags);
-  hipLaunchKernelGGL(k_elem_window, dim3(elem_patches(k.mx, k.mv)),
-                     dim3(ELEMC_WG), 0, c->stream, k, Mc, ctot, cmax, st, rec,
-                     qm, cz, nb, cr, lst, flags, predict, reg);
+  auto kern = own ? (k.per ? k_elem_window<true, true>
+                           : k_elem_window<true, false>)
+                  : (k.per ? k_elem_window<false, true>
+                           : k_elem_window<false, false>);
+  hipLaunchKernelGGL(kern, dim3(elem_patches(k.mx, k.mv)), dim3(ELEMC_WG), 0,
+                     c->stream, k, part, Mc, ctot, cmax, st, rec, qm, cz, nb, cr, lst, flags, predict, reg);
   VP_LAUNCH_CHECK(c, "k_elem_window");
   return VP_OK;
 }

@@ -1114,12 +1114,16 @@ __device__ __forceinline__ double ld_coherent(const double *q) {
 
 // Periodic x: M_right - M_left of eq. (acccomp) at site k in [0, nx)
 // minus the uniform background's own, M_tot (2 k + 1) / nx.
+__device__ __forceinline__ double ring_B(const KP &p, double Mtot, int k,
+                                         double Mk, double Mkm1) {
+  const double bg = Mtot * ((double)(2 * k + 1) / (double)p.nx);
+  return (bg - Mk) - Mkm1;
+}
+
 template <typename MP>
 __device__ __forceinline__ double periodic_B(const KP &p, const MP &M,
                                              double Mtot, int k) {
-  const double bg = Mtot * ((double)(2 * k + 1) / (double)p.nx);
-  const double Lm = (k >= 1) ? M[k - 1] : 0.0;
-  return (bg - M[k]) - Lm;
+  return ring_B(p, Mtot, k, M[k], (k >= 1) ? M[k - 1] : 0.0);
 }
 
 // Mean of B over the ring, summed in the 64-site chunks of M_left (NT
@@ -1177,39 +1181,14 @@ __device__ __forceinline__ void acc_from_mass(const KP &p, const MP &M,
   d2a = ((ap + am) - 2.0 * a0) / dx2;
 }
 
-struct AccFromMass {
+// The same force for one element without the whole table: from a at the
+// sites i0 - 2 .. i0 + 2 around its TSC site i0, a, a', a'' at i0 - 1 .. i0 +
+// 1 with the operations of acc_from_mass (the same values bit for bit).
+struct AccFive {
   const KP &p;
-  const double *M;
-  double Mtot, Bbar;
-  __device__ __forceinline__ void at(int q, double &a, double &da,
-                                     double &d2a) const {
-    acc_from_mass(p, M, Mtot, Bbar, q, a, da, d2a);
-  }
-};
-
-// The same force for one element without the whole M_left table (isolated
-// x): the six cumulative masses M_left(i0 - 3 .. i0 + 2) that the dual TSC
-// around site i0 needs, each the carry of its 64-site chunk plus the
-// chunk's own prefix (mw, read beforehand), give a at i0 - 2 .. i0 + 2 and
-// then a, a', a'' at i0 - 1 .. i0 + 1 with the operations of acc_site and
-// acc_from_mass (the same values bit for bit).
-struct AccWindow {
-  const KP &p;
-  double a[5];  // a at sites i0 - 2 .. i0 + 2
-  int q0;       // table index i0 + 4 of site i0
-  __device__ __forceinline__ AccWindow(const KP &p_, int i0,
-                                       const double *car, const double *mw,
-                                       double Mtot)
-      : p(p_), q0(i0 + 4) {
-    double m[6];
-#pragma unroll
-    for (int d = 0; d < 6; ++d) {
-      const int j = i0 - 3 + d;
-      m[d] = (j < 0) ? 0.0 : (j >= p.nx) ? Mtot : car[j / MCHUNK] + mw[d];
-    }
-#pragma unroll
-    for (int d = 0; d < 5; ++d) a[d] = p.G * ((Mtot - m[d + 1]) - m[d]);
-  }
+  double a[5];
+  int q0;  // table index i0 + 4 of site i0
+  __device__ __forceinline__ AccFive(const KP &p_, int i0) : p(p_), q0(i0 + 4) {}
   __device__ __forceinline__ void at(int q, double &a0, double &da,
                                      double &d2a) const {
     const int k = q - q0;  // -1, 0 or 1
@@ -1219,6 +1198,41 @@ struct AccWindow {
     const double two_dx = 2.0 * p.dx, dx2 = p.dx * p.dx;
     da = (ap - am) / two_dx;
     d2a = ((ap + am) - 2.0 * a0) / dx2;
+  }
+};
+
+// Isolated x: the six cumulative masses M_left(i0 - 3 .. i0 + 2), each the
+// carry of its 64-site chunk plus the chunk's own prefix (mw, read
+// beforehand), and a by acc_site's operations.
+struct AccWindow : AccFive {
+  __device__ __forceinline__ AccWindow(const KP &p_, int i0,
+                                       const double *car, const double *mw,
+                                       double Mtot)
+      : AccFive(p_, i0) {
+    double m[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      const int j = i0 - 3 + d;
+      m[d] = (j < 0) ? 0.0 : (j >= p.nx) ? Mtot : car[j / MCHUNK] + mw[d];
+    }
+#pragma unroll
+    for (int d = 0; d < 5; ++d) a[d] = p.G * ((Mtot - m[d + 1]) - m[d]);
+  }
+};
+
+// Periodic x: a at site i mod nx from the table of B (periodic_B) and its
+// mean.
+struct AccRing : AccFive {
+  __device__ __forceinline__ AccRing(const KP &p_, int i0, const double *B,
+                                     double Bbar)
+      : AccFive(p_, i0) {
+#pragma unroll
+    for (int d = 0; d < 5; ++d) {
+      // sites in [-5, nx + 4] and nx >= 8: at most one period off
+      int k = i0 - 2 + d;
+      k = k < 0 ? k + p.nx : (k >= p.nx ? k - p.nx : k);
+      a[d] = p.G * (B[k] - Bbar);
+    }
   }
 };
 
@@ -1422,6 +1436,13 @@ __global__ __launch_bounds__(FIELD_WG) void k_field_tail(KP p, FieldArgs A) {
 // in identical order (column sums in increasing group order, 64-site chunk
 // prefixes, sequential carries).
 constexpr int FIELD1_MAX = 2048;
+// Element passes whose workgroups form the field's chunks themselves: at most
+// OWN_MAX partials (nx ngy) and OWN_MAX_NX columns.  Measured, us per step with
+// the launch of its own and without (FP64): 256^2 22.5 / 20.0, 512^2 (s = 8)
+// 23.8 / 21.8, 768^2 (9984 partials) 27.6 / 27.0, 1024 x 512 27.4 / 27.3,
+// 1024^2 (17408) 33.2 / 35.4.
+constexpr int OWN_MAX = 10240;
+constexpr int OWN_MAX_NX = 1024;
 
 // M_left of every column into LDS M[0, nx) (NT threads, the whole
 // workgroup); returns M_tot.  With a variable step (p.clk), also the
@@ -1617,24 +1638,37 @@ __global__ __launch_bounds__(64) void k_field_chunks(
 }
 
 // Field and element pass of a step (grids of at most FIELD1_MAX columns,
-// self-consistent force), launched after k_field_chunks on the same stream:
-// every workgroup adds the chunk totals sequentially into carries and takes
-// M_left from the chunks (the whole table with periodic x, else the six
-// values around each element's TSC cell), then kicks, corrects, predicts
-// and registers its elements.  Every load the field needs is issued in one
-// round trip together with the element state.
+// self-consistent force): every workgroup adds the chunk totals sequentially
+// into carries and takes the force from the chunks (isolated x: the six
+// values of M_left around each element's TSC cell; periodic x: the table of
+// B, whose mean needs every site), then kicks, corrects, predicts and
+// registers its elements.  Every load the field needs is issued in one round
+// trip together with the element state.
+//
+// OWN false: the chunks are those of k_field_chunks, the launch before.  OWN
+// true: every workgroup forms all chunks itself from the row groups'
+// partials (the same operations), which saves that launch; its cost grows
+// with the partials, nx ngy.
+//
+// Periodic x: B is formed once per site, by all threads, and its mean summed
+// from the table; elements read five values of it.  With B re-formed at each
+// use (a division and a remainder each, the mean's by 32 of the 256 threads)
+// the pass took 26.2 us at 2048^2 (s = 8, two-stream plasma); now 19.0.
 constexpr int ELEMC_WG = 256;
 static_assert(PATCH * PATCH == ELEMC_WG, "one element per thread");
 
+template <bool OWN, bool PER>
 __global__ __launch_bounds__(ELEMC_WG) void k_elem_window(
-    KP p, const double *__restrict__ Mc, const double *__restrict__ ctot,
-    const double *__restrict__ cmax, double *__restrict__ st,
-    double *__restrict__ rec, double *__restrict__ qm,
+    KP p, const double *__restrict__ part, const double *__restrict__ Mc,
+    const double *__restrict__ ctot, const double *__restrict__ cmax,
+    double *__restrict__ st, double *__restrict__ rec, double *__restrict__ qm,
     int *__restrict__ cnt_zero, long long nb_zero, int *__restrict__ cnt_reg,
     int *__restrict__ lst, int *__restrict__ flags, int predict, int reg) {
-  __shared__ double M[FIELD1_MAX];
+  constexpr int CPT = FIELD1_MAX / ELEMC_WG;  // columns per thread
+  __shared__ double M[OWN ? OWN_MAX_NX : 1];  // chunk prefixes
+  __shared__ double B[PER ? FIELD1_MAX : 1];
   __shared__ double car[FIELD1_MAX / MCHUNK + 1];
-  __shared__ double s_rmax, s_mtot;
+  __shared__ double s_rmax, s_mtot, s_bbar, red[ELEMC_WG / 64];
   const int tid = threadIdx.x, nx = p.nx;
   const int nch = (nx + MCHUNK - 1) / MCHUNK;
   const long long gid = (long long)blockIdx.x * blockDim.x + tid;
@@ -1651,37 +1685,64 @@ __global__ __launch_bounds__(ELEMC_WG) void k_elem_window(
   if (has) elem_load(st, E, e, s);
   // one lane per chunk: the totals, the last prefix and the chunk maxima
   double ct = 0.0, cm = 0.0, mlast = 0.0;
-  if (tid < nch) {
-    ct = ctot[tid];
-    if (p.clk) cm = cmax[tid];
-  }
-  if (tid == 0) mlast = Mc[nx - 1];
-  // isolated x: the six chunk prefixes around the element's TSC cell
-  double mw[6];
+  double mw[6];              // isolated x: the element's chunk prefixes
+  double mc[CPT], mb[CPT];   // periodic x: a site's and the one before it
   int i0 = 0;
-  if (has && !p.per) {
-    double w;
-    i0 = (int)tsc_cell(p, s.x, w);
+  if (OWN) {
+    for (int i = tid; i < nx; i += ELEMC_WG) {
+      // every row group's partial requested ahead of the additions, which go
+      // in increasing group order
+      double x = 0.0;
+      for (int g0 = 0; g0 < p.ngy; g0 += 16) {
+        double v[16];
 #pragma unroll
-    for (int d = 0; d < 6; ++d) {
-      const int j = i0 - 3 + d;
-      mw[d] = (j >= 0 && j < nx) ? Mc[j] : 0.0;
+        for (int u = 0; u < 16; ++u)
+          v[u] = (g0 + u < p.ngy) ? part[(size_t)(g0 + u) * nx + i] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+          if (g0 + u < p.ngy) x += v[u];
+      }
+      const double rho = p.dv * x;
+      M[i] = p.dx * rho;
+      cm = fmax(cm, rho);
+    }
+  } else {
+    if (tid < nch) {
+      ct = ctot[tid];
+      if (p.clk) cm = cmax[tid];
+    }
+    if (tid == 0) mlast = Mc[nx - 1];
+    if (PER) {
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) {
+        const int i = tid + c * ELEMC_WG;
+        mc[c] = i < nx ? Mc[i] : 0.0;
+        mb[c] = (i >= 1 && i < nx) ? Mc[i - 1] : 0.0;
+      }
+    } else if (has) {
+      double w;
+      i0 = (int)tsc_cell(p, s.x, w);
+#pragma unroll
+      for (int d = 0; d < 6; ++d) {
+        const int j = i0 - 3 + d;
+        mw[d] = (j >= 0 && j < nx) ? Mc[j] : 0.0;
+      }
     }
   }
-  // periodic x: the whole table (the mean of B needs every site)
-  if (p.per)
-    for (int i = tid; i < nx; i += ELEMC_WG) M[i] = Mc[i];
   // the counts of the lists the reconstruction has just used, for the next
   // element pass
   for (long long b = gid; b < nb_zero; b += gsz) cnt_zero[b] = 0;
-  if (tid < 64) {
-    if (tid < nch) car[tid] = ct;
-    if (tid == 0) s_mtot = mlast;
-    if (p.clk) {
-      cm = wave_max(cm);
-      if (tid == 0) s_rmax = cm;
-    }
+  if (p.clk) {
+    cm = wave_max(cm);
+    if ((tid & 63) == 0) red[tid >> 6] = cm;
   }
+  if (OWN) {
+    __syncthreads();
+    if (tid < nch)
+      ct = seq_prefix(M + tid * MCHUNK, min(MCHUNK, nx - tid * MCHUNK));
+  }
+  if (tid < nch) car[tid] = ct;
+  if (!OWN && tid == 0) s_mtot = mlast;
   __syncthreads();
   if (tid == 0) {
     // exclusive carries, sequential in chunk order
@@ -1691,28 +1752,67 @@ __global__ __launch_bounds__(ELEMC_WG) void k_elem_window(
       car[k] = carry;
       carry = carry + t;
     }
-    s_mtot = car[nch - 1] + s_mtot;
+    s_mtot = car[nch - 1] + (OWN ? M[nx - 1] : s_mtot);
+    if (p.clk) {
+      double m = 0.0;
+      for (int w = 0; w < ELEMC_WG / 64; ++w) m = fmax(m, red[w]);
+      s_rmax = m;
+    }
   }
   __syncthreads();
-  double Mtot, Bbar = 0.0;
-  if (p.per) {
-    for (int i = tid; i < nx; i += ELEMC_WG) M[i] = car[i / MCHUNK] + M[i];
+  const double Mtot = s_mtot;
+  if (PER) {
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+      const int i = tid + c * ELEMC_WG;
+      if (i < nx) {
+        const double Mi = car[i / MCHUNK] + (OWN ? M[i] : mc[c]);
+        const double Mm =
+            i >= 1 ? car[(i - 1) / MCHUNK] + (OWN ? M[i - 1] : mb[c]) : 0.0;
+        B[i] = ring_B(p, Mtot, i, Mi, Mm);
+      }
+    }
     __syncthreads();
-    Mtot = M[nx - 1];
-    Bbar = periodic_mean<ELEMC_WG>(p, M, Mtot, car);
-  } else {
-    Mtot = s_mtot;
+    // the mean, in the 64-site chunks of periodic_mean
+    if (tid < nch) {
+      const int n = min(MCHUNK, nx - tid * MCHUNK);
+      const double *b = B + tid * MCHUNK;
+      double t = 0.0;
+      for (int q0 = 0; q0 < n; q0 += 16) {
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = q0 + u < n ? b[q0 + u] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+          if (q0 + u < n) t += v[u];
+      }
+      car[tid] = t;  // the carries are not needed any more
+    }
+    __syncthreads();
+    if (tid == 0) {
+      double t = 0.0;
+      for (int c = 0; c < nch; ++c) t = t + car[c];
+      s_bbar = t / (double)nx;
+    }
+    __syncthreads();
   }
   const double dtn = elem_clock(p, p.clk ? s_rmax : 0.0, predict, gid == 0);
   if (has) {
-    if (p.per)
-      elem_kick(p, AccFromMass{p, M, Mtot, Bbar}, s);
-    else {
-      // the cell again, from the same x (equal to i0): the kick's own
-      // tsc_cell then matches it at compile time, and the window's offsets
-      // stay constants
-      double w;
-      const int ic = (int)tsc_cell(p, s.x, w);
+    // the cell (isolated x: again, from the same x): the kick's own tsc_cell
+    // then matches it at compile time, and the window's offsets stay
+    // constants
+    double w;
+    const int ic = (int)tsc_cell(p, s.x, w);
+    if (PER) {
+      elem_kick(p, AccRing(p, ic, B, s_bbar), s);
+    } else {
+      if (OWN) {
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+          const int j = ic - 3 + d;
+          mw[d] = (j >= 0 && j < nx) ? M[j] : 0.0;
+        }
+      }
       elem_kick(p, AccWindow(p, ic, car, mw, Mtot), s);
     }
     if (predict) {
@@ -1722,10 +1822,10 @@ __global__ __launch_bounds__(ELEMC_WG) void k_elem_window(
     elem_store(st, E, e, s);
   }
   if (!predict) return;
-  RegBox B;
-  B.n = 0;
-  if (has) B = elem_record_box(p, s, e, rec, qm, flags, reg);
-  if (B.n > 0) reg_direct(p, B, 0, e, cnt_reg, lst);
+  RegBox R;
+  R.n = 0;
+  if (has) R = elem_record_box(p, s, e, rec, qm, flags, reg);
+  if (R.n > 0) reg_direct(p, R, 0, e, cnt_reg, lst);
 }
 
 // ------------------------------------------------------- reconstruction
