@@ -86,6 +86,7 @@ KP make_kp(const vp_params *p) {
   k.mx = p->nx / p->sx;
   k.mv = p->nv / p->sv;
   k.E = k.mx * k.mv;
+  k.inv_mx = 1.0 / k.mx;
   k.ox = (p->sx / 2) % 8;
   k.ov = (p->sv / 2) % 8;
   k.obx = 1;  // block columns shift with the element drift (group_ox)
@@ -571,26 +572,36 @@ int do_remap(vp_ctx *c) {
 
 // Diagnostics of the current state (positions at the current time): mass,
 // kinetic and potential energy, entropy, max |det T - 1|, E_map, L1, L2
-// into h[8], and the count of overflowed query blocks.  Synchronises the
-// stream.
-int diag_now(vp_ctx *c, double *h, unsigned long long *ovf) {
+// into h[0..7], the count of overflowed query blocks and the flags.
+// Synchronises the stream.
+int diag_now(vp_ctx *c, double *h, unsigned long long *ovf, int *flags) {
   int rc;
   if ((rc = launch_predict(c, 0, 1))) return rc;
   if ((rc = recon<MODE_DIAG>(c, nullptr, nullptr))) return rc;
   if ((rc = launch_zero_counts(c))) return rc;
-  hipLaunchKernelGGL(k_diag, dim3(1), dim3(1024), 0, c->stream, c->k,
-                     c->at<double>(c->L.dpart),
-                     (long long)c->L.nwg_x * c->L.nwg_y,
-                     c->at<double>(c->L.Ml), c->at<double>(c->L.acc),
-                     c->at<double>(c->L.st), c->at<double>(c->L.dout));
+  const long long nwg = (long long)c->L.nwg_x * c->L.nwg_y;
+  // the chunk totals are free until the next field
+  double *gpart = c->at<double>(c->L.ctot);
+  const int n = (int)std::min<long long>(
+      DIAG_WG, grid_for(std::max<long long>(nwg, c->k.E), 256));
+  hipLaunchKernelGGL(k_diag_part, dim3(n), dim3(256), 0, c->stream, c->k,
+                     c->at<double>(c->L.dpart), nwg, c->at<double>(c->L.Ml),
+                     c->at<double>(c->L.acc), c->at<double>(c->L.st), gpart);
+  hipLaunchKernelGGL(k_diag, dim3(1), dim3(64 * DGS), 0, c->stream, c->k,
+                     gpart, n, c->at<double>(c->L.Ml),
+                     c->at<unsigned long long>(c->L.ovf),
+                     c->at<int>(c->L.flags), c->at<double>(c->L.dout));
   VP_LAUNCH_CHECK(c, "k_diag");
-  hipError_t e = hipMemcpyAsync(h, c->at<double>(c->L.dout), 8 * sizeof(double),
+  double out[DOUT_N];
+  hipError_t e = hipMemcpyAsync(out, c->at<double>(c->L.dout), sizeof(out),
                                 hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(ovf, c->at<unsigned long long>(c->L.ovf), sizeof(*ovf),
-                       hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return dev_fail(c, e, "diagnostics read");
+  std::memcpy(h, out, 8 * sizeof(double));
+  std::memcpy(ovf, out + DOUT_OVF, sizeof(*ovf));
+  long long fl = 0;
+  std::memcpy(&fl, out + DOUT_FLAGS, sizeof(fl));
+  *flags = (int)fl;
   return VP_OK;
 }
 
@@ -819,17 +830,21 @@ int read_clock(vp_ctx *c, double *dt, double *t) {
   return VP_OK;
 }
 
+int flags_status(vp_ctx *c, int flags) {
+  if (flags & FLAG_NUMERIC) {
+    c->err = "non-finite element state or det T <= 0 met on the device";
+    return VP_ENUMERIC;
+  }
+  return VP_OK;
+}
+
 int check_flags(vp_ctx *c) {
   int flags = 0;
   hipError_t e = hipMemcpyAsync(&flags, c->at<int>(c->L.flags), sizeof(int),
                                 hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return dev_fail(c, e, "flag read");
-  if (flags & FLAG_NUMERIC) {
-    c->err = "non-finite element state or det T <= 0 met on the device";
-    return VP_ENUMERIC;
-  }
-  return VP_OK;
+  return flags_status(c, flags);
 }
 
 }  // namespace
@@ -996,7 +1011,8 @@ int vp_diagnostics(vp_ctx *c, vp_diag *out) {
   if (!c->ready) return VP_ESTATE;
   double h[8];
   unsigned long long ovf = 0;
-  int rc = diag_now(c, h, &ovf);
+  int flags = 0;
+  int rc = diag_now(c, h, &ovf, &flags);
   if (rc) return rc;
   out->mass = h[0];
   out->e_kin = h[1];
@@ -1010,7 +1026,7 @@ int vp_diagnostics(vp_ctx *c, vp_diag *out) {
   if ((rc = read_clock(c, &out->dt, &out->t))) return rc;
   out->step = c->step;
   out->overflow_blocks = (int64_t)ovf;
-  return check_flags(c);
+  return flags_status(c, flags);
 }
 
 int vp_get_elements(vp_ctx *c, double *el) {

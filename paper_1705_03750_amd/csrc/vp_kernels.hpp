@@ -74,6 +74,7 @@ struct KP {
   long long goxA, goxB;
   // ceil(2^40 / nbx) when it splits every tile index exactly, else 0
   unsigned long long tdm;
+  double inv_mx;  // 1 / mx (elem_lattice)
 };
 
 // The drift at row group gy's central velocity since the elements' last
@@ -1236,6 +1237,13 @@ struct AccRing : AccFive {
   }
 };
 
+// Sum over the 64 lanes of a wavefront, pairwise.
+__device__ __forceinline__ double wave_sum(double s) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  return s;
+}
+
 // Largest value over the 64 lanes of a wavefront (order-free: max is exact).
 __device__ __forceinline__ double wave_max(double m) {
 #pragma unroll
@@ -1830,6 +1838,14 @@ __global__ __launch_bounds__(ELEMC_WG) void k_elem_window(
 
 // ------------------------------------------------------- reconstruction
 
+// Lattice row l and column k of element e < 2^30: the quotient by mx from a
+// multiplication, (e + 1/2) / mx being at least 2^-18 away from an integer.
+__device__ __forceinline__ void elem_lattice(const KP &p, int e, int &k,
+                                             int &l) {
+  l = (int)(((double)e + 0.5) * p.inv_mx);
+  k = e - l * p.mx;
+}
+
 // Lattice neighbour column k of an element (k may be -1 or mx): -1 when
 // there is none; with periodic x the columns wrap and the wrapped
 // neighbour's Lagrangian position moves by one period (shift).
@@ -1900,8 +1916,11 @@ __device__ __forceinline__ void recon_tile(
     if (MODE == MODE_ASSIGN && live) aout[(size_t)j * p.nx + i] = best;
     if ((MODE == MODE_DIAG || MODE == MODE_EMAP) && live && best >= 0) {
       // E_map at this site: distance between the nearest element's
-      // prediction of Q and those of its valid lattice neighbours
-      const int l0 = best / p.mx, k0 = best - l0 * p.mx;
+      // prediction of Q and those of its valid lattice neighbours, squared
+      // (the root is taken of the workgroup's largest: the same value, the
+      // rounded root being monotonic)
+      int k0, l0;
+      elem_lattice(p, best, k0, l0);
       const double qx0 = qm[2 * (size_t)best] + dqx;
       const double qv0 = qm[2 * (size_t)best + 1] + dqv;
       const int nk[4] = {-1, 1, 0, 0}, nl[4] = {0, 0, -1, 1};
@@ -1916,7 +1935,7 @@ __device__ __forceinline__ void recon_tile(
         const double mx = ((qm[2 * m] + shift) + ex) - qx0;
         const double mv = (qm[2 * m + 1] + ev) - qv0;
         const double zx = mx * p.rx, zv = mv * p.rv;
-        em = fmax(em, sqrt(fma(zx, zx, zv * zv)));
+        em = fmax(em, fma(zx, zx, zv * zv));
       }
     }
   }
@@ -1930,7 +1949,7 @@ __device__ __forceinline__ void recon_tile(
       double m = swm[0];
 #pragma unroll
       for (int k = 1; k < 8; ++k) m = fmax(m, swm[k]);
-      dpart[DPS * ((size_t)gy * p.nbx + bx) + DP_EMAP] = m;
+      dpart[DPS * ((size_t)gy * p.nbx + bx) + DP_EMAP] = sqrt(m);
     }
     return;
   }
@@ -1977,7 +1996,7 @@ __device__ __forceinline__ void recon_tile(
       const size_t wg = (size_t)gy * p.nbx + bx;
       dpart[DPS * wg + DP_KIN] = sk[0];
       dpart[DPS * wg + DP_ENT] = se[0];
-      dpart[DPS * wg + DP_EMAP] = sm[0];
+      dpart[DPS * wg + DP_EMAP] = sqrt(sm[0]);
       dpart[DPS * wg + DP_L1] = s1[0];
       dpart[DPS * wg + DP_L2] = s2[0];
     }
@@ -2046,7 +2065,8 @@ __device__ __forceinline__ void remap_tile(
   const bool ring = (j == 0 || j == p.nv - 1) ||
                     (!PER && (i == 0 || i == p.nx - 1));
   if (!ring && best >= 0) {
-    const int l0 = best / p.mx, k0 = best - l0 * p.mx;
+    int k0, l0;
+    elem_lattice(p, best, k0, l0);
     const double zx = dqx * p.rx, zv = dqv * p.rv, beta = p.beta;
     const int xlo = (zx < beta) ? -1 : 0, xhi = (zx < -beta) ? 0 : 1;
     const int vlo = (zv < beta) ? -1 : 0, vhi = (zv < -beta) ? 0 : 1;
@@ -2118,9 +2138,6 @@ __global__ __launch_bounds__(512) void k_remap_eval(
                             gy);
 }
 
-// Diagnostics (section 3.2): sums of the per-workgroup partials, potential
-// energy from a(i), max |det T - 1|.  out = {mass, e_kin, e_pot, entropy,
-// maxdet}.
 // E_map alone (the adaptive resampling check): the largest of the
 // workgroups' site maxima written by the MODE_EMAP (or MODE_DIAG)
 // reconstruction, into out[5] as k_diag does.
@@ -2140,81 +2157,105 @@ __global__ __launch_bounds__(1024) void k_emap_max(
   if (tid == 0) out[5] = sm[0];
 }
 
-__global__ __launch_bounds__(1024) void k_diag(
+// Diagnostics (section 3.2) in two launches: k_diag_part sums a share of the
+// reconstruction's per-workgroup partials, of the potential energy from a(i)
+// (or phi_ext) and of the elements' |det T - 1| into gpart[DG][workgroup];
+// k_diag adds the shares in order.  One workgroup over everything took 37 us
+// at 2048^2 (65536 elements) and 937 us at 8192^2 and 16384^2, all of it load
+// latency; at 2048^2 the two take 4.8 + 5.7 us.
+// out = {mass, e_kin, e_pot, entropy, maxdet, emap, l1, l2} and, for the
+// host's one read, the overflow count and the flags (as bits).
+enum { DG_POT = DPS, DG_DET, DGS };
+constexpr int DIAG_WG = 256;  // most workgroups of k_diag_part
+static_assert(DGS * DIAG_WG <= FIELD_CHUNKS, "gpart is the chunk totals");
+constexpr int DOUT_OVF = 8, DOUT_FLAGS = 9, DOUT_N = 10;
+
+__global__ __launch_bounds__(256) void k_diag_part(
     KP p, const double *__restrict__ dpart, long long nwg,
     const double *__restrict__ Ml, const double *__restrict__ acc,
-    const double *__restrict__ st, double *__restrict__ out) {
-  __shared__ double s0[1024], s1[1024], s2[1024], s3[1024], s4[1024],
-      s5[1024], s6[1024];
+    const double *__restrict__ st, double *__restrict__ gpart) {
   const int tid = threadIdx.x;
-  double kin = 0.0, ent = 0.0, pot = 0.0, mdet = 0.0, emap = 0.0, l1 = 0.0,
-         l2 = 0.0;
-  for (long long q = tid; q < nwg; q += blockDim.x) {
-    kin += dpart[DPS * q + DP_KIN];
-    ent += dpart[DPS * q + DP_ENT];
-    emap = fmax(emap, dpart[DPS * q + DP_EMAP]);
-    l1 += dpart[DPS * q + DP_L1];
-    l2 += dpart[DPS * q + DP_L2];
+  const long long g0 = (long long)blockIdx.x * 256 + tid;
+  const long long gsz = (long long)gridDim.x * 256;
+  double v[DGS] = {};
+  for (long long q = g0; q < nwg; q += gsz) {
+#pragma unroll
+    for (int d = 0; d < DPS; ++d) {
+      const double x = dpart[DPS * q + d];
+      v[d] = (d == DP_EMAP) ? fmax(v[d], x) : v[d] + x;
+    }
   }
-  const double Mtot = Ml[p.nx - 1];
-  const int n8 = p.nx + 8;
   if (p.force_mode == 0) {
     // periodic x: the field energy of the zero-mean force alone
-    const double GM = p.per ? 0.0 : p.G * Mtot;
-    for (int i = tid; i < p.nx; i += blockDim.x) {
+    const double GM = p.per ? 0.0 : p.G * Ml[p.nx - 1];
+    for (long long i = g0; i < p.nx; i += gsz) {
       const double a = acc[i + 4];
-      pot += a * a - GM * GM;
+      v[DG_POT] += a * a - GM * GM;
     }
   } else {
-    for (int i = tid; i < p.nx; i += blockDim.x) {
-      const double x = site_x(p, i);
+    for (long long i = g0; i < p.nx; i += gsz) {
+      const double x = site_x(p, (int)i);
       const double phi =
           -(x * (p.a0 + x * (0.5 * p.a1 + x * (p.a2 / 3.0))));
       // rho(i) dx = M(i) = Ml(i) - Ml(i-1)
       const double Mi = Ml[i] - (i > 0 ? Ml[i - 1] : 0.0);
-      pot += phi * Mi;
+      v[DG_POT] += phi * Mi;
     }
   }
   const size_t E = (size_t)p.E;
-  for (int e = tid; e < p.E; e += blockDim.x) {
+  for (long long e = g0; e < p.E; e += gsz) {
     const double det = st[S_TXX * E + e] * st[S_TVV * E + e] -
                        st[S_TXV * E + e] * st[S_TVX * E + e];
-    mdet = fmax(mdet, fabs(det - 1.0));
+    v[DG_DET] = fmax(v[DG_DET], fabs(det - 1.0));
   }
-  (void)n8;
-  s0[tid] = kin;
-  s1[tid] = ent;
-  s2[tid] = pot;
-  s3[tid] = mdet;
-  s4[tid] = emap;
-  s5[tid] = l1;
-  s6[tid] = l2;
+  __shared__ double sm[DGS][4];
+#pragma unroll
+  for (int d = 0; d < DGS; ++d) {
+    const double x =
+        (d == DP_EMAP || d == DG_DET) ? wave_max(v[d]) : wave_sum(v[d]);
+    if ((tid & 63) == 0) sm[d][tid >> 6] = x;
+  }
   __syncthreads();
-  for (int s = 512; s > 0; s >>= 1) {
-    if (tid < s) {
-      s0[tid] += s0[tid + s];
-      s1[tid] += s1[tid + s];
-      s2[tid] += s2[tid + s];
-      s3[tid] = fmax(s3[tid], s3[tid + s]);
-      s4[tid] = fmax(s4[tid], s4[tid + s]);
-      s5[tid] += s5[tid + s];
-      s6[tid] += s6[tid + s];
-    }
-    __syncthreads();
+  if (tid < DGS) {
+    double t = sm[tid][0];
+    for (int w = 1; w < 4; ++w)
+      t = (tid == DP_EMAP || tid == DG_DET) ? fmax(t, sm[tid][w])
+                                            : t + sm[tid][w];
+    gpart[(size_t)tid * gridDim.x + blockIdx.x] = t;
   }
-  if (tid == 0) {
+}
+
+__global__ __launch_bounds__(64 * DGS) void k_diag(
+    KP p, const double *__restrict__ gpart, int n,
+    const double *__restrict__ Ml, const unsigned long long *__restrict__ ovf,
+    const int *__restrict__ flags, double *__restrict__ out) {
+  // one wavefront per quantity
+  __shared__ double s[DGS];
+  const int d = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const bool mx = d == DP_EMAP || d == DG_DET;
+  double t = 0.0;
+  for (int q = lane; q < n; q += 64) {
+    const double x = gpart[(size_t)d * n + q];
+    t = mx ? fmax(t, x) : t + x;
+  }
+  t = mx ? wave_max(t) : wave_sum(t);
+  if (lane == 0) s[d] = t;
+  __syncthreads();
+  if (threadIdx.x == 0) {
     const double cell = p.dx * p.dv;
-    out[0] = Mtot;
-    out[1] = 0.5 * s0[0] * cell;
+    out[0] = Ml[p.nx - 1];
+    out[1] = 0.5 * s[DP_KIN] * cell;
     if (p.force_mode == 0)
-      out[2] = (p.G != 0.0) ? -s2[0] * p.dx / (4.0 * p.G) : 0.0;
+      out[2] = (p.G != 0.0) ? -s[DG_POT] * p.dx / (4.0 * p.G) : 0.0;
     else
-      out[2] = s2[0];
-    out[3] = -s1[0] * cell;
-    out[4] = s3[0];
-    out[5] = s4[0];
-    out[6] = s5[0] * cell;
-    out[7] = sqrt(s6[0] * cell);
+      out[2] = s[DG_POT];
+    out[3] = -s[DP_ENT] * cell;
+    out[4] = s[DG_DET];
+    out[5] = s[DP_EMAP];
+    out[6] = s[DP_L1] * cell;
+    out[7] = sqrt(s[DP_L2] * cell);
+    out[DOUT_OVF] = __longlong_as_double((long long)ovf[0]);
+    out[DOUT_FLAGS] = __longlong_as_double((long long)flags[0]);
   }
 }
 
