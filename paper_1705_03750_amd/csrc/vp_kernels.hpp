@@ -2692,15 +2692,20 @@ __global__ __launch_bounds__(256) void k_ghost_x(KP p, FT *__restrict__ C) {
 // Periodic x, cyclic spline system (Sherman-Morrison): T holds y = B^-1 6F
 // per row (B the tridiagonal part, diagonal 8, 4, .., 4, 4.25); with z =
 // B^-1 (-4, 0, .., 0, 1) the coefficients are y - [(y_0 - y_{n-1}/4) / den]
-// z, den = (1 + z_0) - z_{n-1}/4.  One workgroup per row.
+// z, den = (1 + z_0) - z_{n-1}/4.  One workgroup per row.  y_0 and y_{n-1}
+// go through LDS: read by every thread, the loads are uniform and may be
+// scheduled after the barrier (T is restrict), where another wavefront has
+// already replaced y_0.
 template <typename FT>
 __global__ __launch_bounds__(256) void k_fit_x_cyclic(
     KP p, FT *__restrict__ T, const FT *__restrict__ z,
     const FT *__restrict__ den) {
   FT *row = T + (size_t)blockIdx.x * p.nx;
-  const FT num = row[0] - (FT)0.25 * row[p.nx - 1];
+  __shared__ FT ends[2];
+  if (threadIdx.x < 2) ends[threadIdx.x] = row[threadIdx.x ? p.nx - 1 : 0];
+  __syncthreads();  // y_0 and y_{n-1} are read
+  const FT num = ends[0] - (FT)0.25 * ends[1];
   const FT fact = num / den[0];
-  __syncthreads();  // every thread has read y_0 and y_{n-1}
   for (int i = threadIdx.x; i < p.nx; i += 256) row[i] = row[i] - fact * z[i];
 }
 
