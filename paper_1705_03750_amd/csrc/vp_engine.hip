@@ -447,7 +447,8 @@ int fit_spline_t(vp_ctx *c, hipStream_t st) {
   FT *tab = c->at<FT>(c->L.tab);
   FT *zx = tab + 2 * k.nx + 2 * k.nv, *den = tab + 3 * k.nx + 2 * k.nv;
   hipLaunchKernelGGL((k_fit_x<FT>),
-                     dim3(grid_for(k.nv, FIT_LINES) * fit_segments<FT>(k.nx)),
+                     dim3(grid_for(k.nv, FIT_LINES) *
+                          fit_segments<FT>(k.nx, k.nv)),
                      dim3(FIT_THREADS), 0,
                      st, k, c->at<FT>(c->L.F), c->at<FT>(c->L.T), tab);
   VP_LAUNCH_CHECK(c, "k_fit_x");
@@ -457,7 +458,8 @@ int fit_spline_t(vp_ctx *c, hipStream_t st) {
     VP_LAUNCH_CHECK(c, "k_fit_x_cyclic");
   }
   hipLaunchKernelGGL((k_fit_v<FT>),
-                     dim3(grid_for(k.nx, FIT_LINES) * fit_segments<FT>(k.nv)),
+                     dim3(grid_for(k.nx, FIT_LINES) *
+                          fit_segments<FT>(k.nv, k.nx)),
                      dim3(FIT_THREADS), 0,
                      st, k, c->at<FT>(c->L.T), c->at<FT>(c->L.C), tab);
   VP_LAUNCH_CHECK(c, "k_fit_v");
@@ -1466,10 +1468,10 @@ void build_tick(vp_server *s, PhaseTable *tab, std::vector<int> &finishing) {
       const int hr = 2 * (step_after - (int)c->reset_step);
       add(PH_RM_PRED, q, el_items, EA_PRED | EA_REG | regr | tb, hr);
       add(PH_RM_EVAL, q, tiles, cr, hr);
-      const int sx = c->mixed() ? fit_segments<float>(k.nx)
-                                : fit_segments<double>(k.nx);
-      const int sv = c->mixed() ? fit_segments<float>(k.nv)
-                                : fit_segments<double>(k.nv);
+      const int sx = c->mixed() ? fit_segments<float>(k.nx, k.nv)
+                                : fit_segments<double>(k.nx, k.nv);
+      const int sv = c->mixed() ? fit_segments<float>(k.nv, k.nx)
+                                : fit_segments<double>(k.nv, k.nx);
       add(PH_FIT_X, q, ceil_div(k.nv, 64) * sx, 0);
       add(PH_FIT_V, q, ceil_div(k.nx, 64) * sv, 0);
       add(PH_GHOST, q, ceil_div(k.nv + 2, 256), 0);

@@ -2272,7 +2272,7 @@ __global__ __launch_bounds__(64 * DGS) void k_diag(
 // back).  Forward sweep, then back substitution over the tiles in reverse.
 //
 // Long lines are solved in segments, so that a line's recurrences run in
-// parallel instead of one after another: a segment of FIT_SEG_TILES tiles
+// parallel instead of one after another: a segment of 1 to 8 tiles
 // is solved over its positions extended by one tile on each side, as the
 // system truncated there (its first row without the sub-diagonal, its last
 // without the super-diagonal).  The inverse of the (1, 4, 1) matrix decays
@@ -2288,7 +2288,7 @@ constexpr int FIT_LINES = 64;
 constexpr int FIT_MOVERS = 256;                 // wavefronts 1-4
 constexpr int FIT_THREADS = 64 + FIT_MOVERS;
 constexpr int FIT_NB = 3;
-constexpr int FIT_SEG_TILES = 8;
+constexpr int FIT_SEG_TILES = 8;                // longest segment
 constexpr int FIT_TW_MAX = 64;  // tile width of the float fit
 
 template <typename FT>
@@ -2304,11 +2304,30 @@ static_assert(FitLds<float>::NV * 4 * FIT_MOVERS == FIT_LINES * 64, "tile");
 static_assert(FitLds<double>::NV * 2 * FIT_MOVERS == FIT_LINES * 32, "tile");
 static_assert(FitLds<float>::TW == FIT_TW_MAX, "artificial pivot table");
 
-// Segments of a line of n positions (each FIT_SEG_TILES tiles, the last
-// one shorter).
+// Tiles per segment for nl lines of n positions: the fewest of 1, 2, 4 and 8
+// that keep the pass at FIT_WGS workgroups or less.  A workgroup's time is
+// the chain of its tiles, so a grid that leaves compute units idle takes
+// short segments; the two extension tiles are loaded and eliminated once
+// more per segment, which costs more than it gives once the chip is full.
+// Both passes of a fit, us, with segments of 8 / 4 / 2 / 1 tiles: FP64 256^2
+// 51 / 34 / 26 / 22, 1024^2 57 / 36 / 29 / 37, 8192 x 256 59 / 40 / 49 / 64,
+// 2048^2 65 / 70 / 86 / 117; mixed 1024^2 57 / 40 / 31 / 28, 2048^2
+// 61 / 44 / 40 / 64, 4096^2 110 / 136 / 155 / 198.  A function of the grid
+// alone, so that a served run and the same run by itself agree bit for bit.
 template <typename FT>
-__host__ __device__ __forceinline__ int fit_segments(int n) {
-  constexpr int m = FIT_SEG_TILES * FitLds<FT>::TW;
+__host__ __device__ __forceinline__ int fit_seg_tiles(int n, int nl) {
+  constexpr int TW = FitLds<FT>::TW, FIT_WGS = 8 * TW;
+  const long chunks = (nl + FIT_LINES - 1) / FIT_LINES;
+  const int tiles = (n + TW - 1) / TW;
+  int t = 1;
+  while (t < FIT_SEG_TILES && chunks * ((tiles + t - 1) / t) > FIT_WGS) t *= 2;
+  return t;
+}
+
+// Segments of a line of n positions of such a pass (the last one shorter).
+template <typename FT>
+__host__ __device__ __forceinline__ int fit_segments(int n, int nl) {
+  const int m = fit_seg_tiles<FT>(n, nl) * FitLds<FT>::TW;
   return (n + m - 1) / m;
 }
 
@@ -2489,7 +2508,21 @@ __device__ __forceinline__ FT fit_sweep(const FitLine<FT> &G, FitLds<FT> &S,
       if (!BACK && i0 >= G.sb) {
         // the tile after the segment: eliminate, and sum the back
         // substitution from its end down to sb
-        for (int k = 0; k < kn; ++k) {
+        for (int k0 = 0; k0 < kb; k0 += 16) {
+          FT v[16], c[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u) {
+            v[u] = col[(k0 + u) * LP];
+            c[u] = cf[k0 + u];
+          }
+#pragma unroll
+          for (int u = 0; u < 16; ++u) {
+            acc = ((FT)6 * v[u] - acc) * c[u];
+            csum = fma(w, acc, csum);
+            w = -w * c[u];
+          }
+        }
+        for (int k = kb; k < kn; ++k) {
           const FT sd = (G.last2 && i0 + k == n - 1) ? (FT)2 * acc : acc;
           acc = ((FT)6 * col[k * LP] - sd) * cf[k];
           csum = fma(w, acc, csum);
@@ -2574,8 +2607,10 @@ __device__ __forceinline__ FT fit_sweep(const FitLine<FT> &G, FitLds<FT> &S,
 // eliminated range [pb, pe), extended by one tile where the segment does not
 // reach the line's end.
 template <typename FT>
-__device__ __forceinline__ void fit_segment(FitLine<FT> &G, int seg) {
-  constexpr int TW = FitLds<FT>::TW, m = FIT_SEG_TILES * TW;
+__device__ __forceinline__ void fit_segment(FitLine<FT> &G, int seg,
+                                            int tiles) {
+  constexpr int TW = FitLds<FT>::TW;
+  const int m = tiles * TW;
   G.sa = seg * m;
   G.sb = min(G.n, G.sa + m);
   G.pb = (G.sa > 0) ? G.sa - TW : 0;
@@ -2601,7 +2636,7 @@ __device__ __forceinline__ void fit_x_rows(const KP &p, const FT *__restrict__ F
                                           const FT *__restrict__ tab,
                                           const int w, FitLds<FT> &S) {
   const FitTables<FT> tb(p, tab);
-  const int nseg = fit_segments<FT>(p.nx);
+  const int nseg = fit_segments<FT>(p.nx, p.nv);
   const int chunk = w / nseg, seg = w - chunk * nseg;
   const int j0 = chunk * FIT_LINES;
   FitLine<FT> G;
@@ -2616,7 +2651,7 @@ __device__ __forceinline__ void fit_x_rows(const KP &p, const FT *__restrict__ F
   G.coef = tb.rix;
   G.coef_art = tb.art;
   G.last2 = !p.per;  // periodic x: the cyclic system's tridiagonal part
-  fit_segment<FT>(G, seg);
+  fit_segment<FT>(G, seg, fit_seg_tiles<FT>(p.nx, p.nv));
   const FT cb = fit_sweep<FT, false, false, false>(G, S);
   G.in = G.out;
   G.in_ls = G.out_ls;
@@ -2632,7 +2667,7 @@ __device__ __forceinline__ void fit_v_cols(const KP &p, const FT *__restrict__ T
                                           const FT *__restrict__ tab,
                                           const int w, FitLds<FT> &S) {
   const FitTables<FT> tb(p, tab);
-  const int nseg = fit_segments<FT>(p.nv);
+  const int nseg = fit_segments<FT>(p.nv, p.nx);
   const int chunk = w / nseg, seg = w - chunk * nseg;
   const int i0 = chunk * FIT_LINES;
   FitLine<FT> G;
@@ -2647,7 +2682,7 @@ __device__ __forceinline__ void fit_v_cols(const KP &p, const FT *__restrict__ T
   G.coef = tb.riv;
   G.coef_art = tb.art;
   G.last2 = 1;
-  fit_segment<FT>(G, seg);
+  fit_segment<FT>(G, seg, fit_seg_tiles<FT>(p.nv, p.nx));
   const FT cb = fit_sweep<FT, true, false, false>(G, S);
   G.in = G.out;
   G.in_ps = G.out_ps;
