@@ -464,7 +464,8 @@ int fit_spline_t(vp_ctx *c, hipStream_t st) {
                      st, k, c->at<FT>(c->L.T), c->at<FT>(c->L.C), tab);
   VP_LAUNCH_CHECK(c, "k_fit_v");
   if (k.per) {
-    hipLaunchKernelGGL((k_ghost_periodic<FT>), dim3(grid_for(k.nv + 2, 256)),
+    hipLaunchKernelGGL((k_ghost_periodic<FT>),
+                       dim3(grid_for(2LL * PX * (k.nv + 2), 256)),
                        dim3(256), 0, st, k, c->at<FT>(c->L.C), -1,
                        k.nv);
     VP_LAUNCH_CHECK(c, "k_ghost_periodic");
@@ -479,7 +480,8 @@ int fit_spline_t(vp_ctx *c, hipStream_t st) {
 // Periodic x: the ghost columns of F_ini after its interior was written.
 template <typename FT>
 int ghost_F_t(vp_ctx *c) {
-  hipLaunchKernelGGL((k_ghost_periodic<FT>), dim3(grid_for(c->k.nv, 256)),
+  hipLaunchKernelGGL((k_ghost_periodic<FT>),
+                     dim3(grid_for(2LL * PX * c->k.nv, 256)),
                      dim3(256), 0, c->stream, c->k, c->at<FT>(c->L.F), 0,
                      c->k.nv - 1);
   VP_LAUNCH_CHECK(c, "k_ghost_periodic");
