@@ -1213,11 +1213,16 @@ extern "C" int vp_poisson_static(const vp_params *p, const double *rho,
   A.a_out = a;
   A.da_out = da;
   A.d2a_out = d2a;
-  // the finished-chunk counter starts at zero (a fill kernel, so that the
-  // call can be captured into a graph)
-  hipLaunchKernelGGL(k_fill<int>, dim3(1), dim3(64), 0, s, A.fcnt, 1LL, 0);
-  hipError_t e = hipGetLastError();
+  // the finished-chunk counter of the column-chunk kernel starts at zero (a
+  // fill kernel, so that the call can be captured into a graph); the
+  // one-workgroup field has none.  256 columns, us per call: 15.9 with the
+  // second launch, 12.9 without
+  hipError_t e = hipSuccess;
   const char *where = "k_fill";
+  if (k.nx > FIELD1_MAX) {
+    hipLaunchKernelGGL(k_fill<int>, dim3(1), dim3(64), 0, s, A.fcnt, 1LL, 0);
+    e = hipGetLastError();
+  }
   if (e == hipSuccess) e = field_launches(k, A, s, &where);
   if (e != hipSuccess) {
     g_create_error = std::string(where) + ": " + hipGetErrorString(e);
