@@ -1,14 +1,15 @@
 // vp_batch.hpp -- batched kernels of the serving loop: one launch advances
 // many independent runs (different grids, element strides and step counts).
 //
-// Every kernel has a fixed grid and walks a per-phase work table: item ids
+// Every kernel walks a per-phase work table, whatever its grid: item ids
 // [0, total) are split among the runs of the phase (table entry = run slot,
 // first item, per-run argument).  A workgroup finds its run by a uniform
 // binary search, then calls exactly the same per-tile device routine as the
 // single-run kernels, so a run's arithmetic does not depend on its
-// batch-mates and its results are bitwise those of a run alone.  Because the
-// grids are fixed and all variability lives in device tables, the sequence
-// of launches of one tick is captured once in a HIP graph and replayed.
+// batch-mates and its results are bitwise those of a run alone.  All
+// variability lives in device tables, so the launches of a tick in which no
+// run starts, resamples or finishes are captured once in a HIP graph, at fixed
+// grids, and replayed; other ticks launch the phases that have items.
 #pragma once
 
 #include "vp_kernels.hpp"
