@@ -78,12 +78,20 @@ __device__ __forceinline__ int find_run(const PhaseTable *__restrict__ t,
 // Element passes (predict / kick / remap records / reset / count clearing):
 // 256 elements and 256 block counts per item; with EA_TAB the item's
 // elements are lattice patch item - begin and their slot claims go through
-// the workgroup's table (the flag is uniform over an item, so every thread
-// of the workgroup reaches the table's barriers).
+// the workgroup's table.  Every flag is uniform over an item, so every thread
+// of the workgroup reaches its barriers.
+//
+// The kick on grids of at most FIELD1_MAX columns takes the cumulative mass
+// around its element from the chunks that kb_field leaves, as the single-run
+// element pass does; wider grids read the force from its table.  Bound by
+// the latency of its loads at three wavefronts per SIMD (154 VGPRs; held to
+// 128 it spills and 24 served runs take 87.5 ms, against 83.0).
 template <typename FT>
 __global__ __launch_bounds__(256) void kb_elem(
     const RunDesc<FT> *__restrict__ runs, const PhaseTable *__restrict__ tab) {
   __shared__ int rtab[RT * RT];
+  __shared__ double car[FIELD1_MAX / MCHUNK + 1];
+  __shared__ double s_mtot;
   const int total = tab->total;
   const int tid = threadIdx.x;
   for (int item = blockIdx.x; item < total; item += gridDim.x) {
@@ -94,12 +102,9 @@ __global__ __launch_bounds__(256) void kb_elem(
     p.tau = 0.5 * p.dt * pi.h;
     gox_set(p);
     const int arg = pi.arg;
-    const bool tabm = arg & EA_TAB;
-    if (tabm) {
-      // the previous item's table reads are done before it is cleared
-      __syncthreads();
-      for (int i = tid; i < RT * RT; i += 256) rtab[i] = 0;
-    }
+    const bool tabm = arg & EA_TAB, kick = arg & EA_KICK,
+               drift = arg & EA_DRIFT, pred = arg & EA_PRED;
+    const bool win = kick && p.force_mode != 1 && p.nx <= FIELD1_MAX;
     const int local = item - pi.begin;
     const long long idx = (long long)local * 256 + tid;
     if (arg & EA_ZERO) {
@@ -114,31 +119,8 @@ __global__ __launch_bounds__(256) void kb_elem(
                           : idx < p.E;
     const int e = !has ? 0 : tabm ? el * p.mx + ek : (int)idx;
     const size_t E = (size_t)p.E;
-    if (tabm) {
-      const bool kick = arg & EA_KICK, drift = arg & EA_DRIFT;
-      ElemState s;
-      RegBox B;
-      B.n = 0;
-      if (has) {
-        elem_load(R.st, E, e, s);
-        if (kick) elem_kick(p, AccTable{R.acc, p.nx + 8}, s);
-        if (drift) elem_drift(p, s);
-        if (kick || drift) elem_store(R.st, E, e, s);
-        B = elem_record_box(p, s, e, R.rec, R.qm, R.flags,
-                            (arg & EA_REG) ? 1 : 0);
-      }
-      const int tr0 =
-          blk(p.sv * ((local / npx) * PATCH + PATCH / 2), p.ov, p.obv) -
-          RT / 2;
-      const int tc0 =
-          blk(p.sx * ((local % npx) * PATCH + PATCH / 2), 0, 1) - RT / 2;
-      __syncthreads();  // the cleared table
-      reg_table<TABLE_RB>(p, B, e, tr0, tc0, rtab,
-                          R.cnt + ((arg & EA_REGBUF1) ? R.nb : 0), R.lst);
-      continue;
-    }
-    if (!has) continue;
     if (arg & EA_RESET) {
+      if (!has) continue;
       const int k = e % p.mx, l = e / p.mx;
       for (int s = 0; s < NSTATE; ++s) R.st[s * E + e] = 0.0;
       R.st[S_X * E + e] = site_x(p, p.sx * k + p.sx / 2);
@@ -147,18 +129,68 @@ __global__ __launch_bounds__(256) void kb_elem(
       R.st[S_TVV * E + e] = 1.0;
       continue;
     }
-    const bool kick = arg & EA_KICK, drift = arg & EA_DRIFT,
-               pred = arg & EA_PRED;
     if (!kick && !pred) continue;
     ElemState s;
-    elem_load(R.st, E, e, s);
-    if (kick) elem_kick(p, AccTable{R.acc, p.nx + 8}, s);
-    if (pred && drift) elem_drift(p, s);
-    if (kick || (pred && drift)) elem_store(R.st, E, e, s);
-    if (pred)
-      elem_record(p, s, e, R.rec, R.qm,
-                  R.cnt + ((arg & EA_REGBUF1) ? R.nb : 0), R.lst, R.flags,
-                  (arg & EA_REG) ? 1 : 0);
+    if (has) elem_load(R.st, E, e, s);
+    if (tabm || win) {
+      // the previous item's reads of the LDS are done before it is rewritten
+      __syncthreads();
+      if (tabm)
+        for (int i = tid; i < RT * RT; i += 256) rtab[i] = 0;
+    }
+    if (win) {
+      const int nch = (p.nx + MCHUNK - 1) / MCHUNK;
+      double w, mw[6];
+      if (has) {
+        const int ic = (int)tsc_cell(p, s.x, w);
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+          const int j = ic - 3 + d;
+          mw[d] = (j >= 0 && j < p.nx) ? R.Mc[j] : 0.0;
+        }
+      }
+      if (tid < nch) car[tid] = R.ctot[tid];
+      __syncthreads();
+      if (tid == 0) {
+        // exclusive carries, sequential in chunk order
+        double carry = 0.0;
+        for (int k = 0; k < nch; ++k) {
+          const double t = car[k];
+          car[k] = carry;
+          carry = carry + t;
+        }
+        s_mtot = car[nch - 1] + R.Mc[p.nx - 1];
+      }
+      __syncthreads();
+      if (has) {
+        // the cell again, so that the kick's own matches it at compile time
+        // and the window's offsets stay constants
+        const int ic = (int)tsc_cell(p, s.x, w);
+        elem_kick(p, AccWindow(p, ic, car, mw, s_mtot), s);
+      }
+    } else if (kick && has) {
+      elem_kick(p, AccTable{R.acc, p.nx + 8}, s);
+    }
+    if (has && pred && drift) elem_drift(p, s);
+    if (has && (kick || (pred && drift))) elem_store(R.st, E, e, s);
+    if (!pred) continue;
+    RegBox B;
+    B.n = 0;
+    if (has)
+      B = elem_record_box(p, s, e, R.rec, R.qm, R.flags,
+                          (arg & EA_REG) ? 1 : 0);
+    int *cnt = R.cnt + ((arg & EA_REGBUF1) ? R.nb : 0);
+    if (tabm) {
+      const int tr0 =
+          blk(p.sv * ((local / npx) * PATCH + PATCH / 2), p.ov, p.obv) -
+          RT / 2;
+      const int tc0 =
+          blk(p.sx * ((local % npx) * PATCH + PATCH / 2), 0, 1) - RT / 2;
+      __syncthreads();  // the cleared table
+      reg_table<TABLE_RB>(p, B, e, tr0, tc0, rtab, cnt, R.lst);
+    } else if (B.n > 0) {
+      reg_direct(p, B, 0, e, cnt, R.lst);
+    }
   }
 }
 
@@ -186,7 +218,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8))) void k
   }
 }
 
-// Field chunks (256 columns per item) from the row-group partials.
+// The field, 256 columns per item, from the row-group partials: on grids of
+// at most FIELD1_MAX columns the chunks of the cumulative mass, one per
+// wavefront, for the kick to finish; else the force table, by the run's last
+// workgroup (20 us a launch in the mix of 24 runs for the table of all of
+// them, 7.5 for the chunks).
 template <typename FT>
 __global__ __launch_bounds__(FIELD_WG) void kb_field(
     const RunDesc<FT> *__restrict__ runs, const PhaseTable *__restrict__ tab) {
@@ -197,6 +233,14 @@ __global__ __launch_bounds__(FIELD_WG) void kb_field(
     const int q = find_run(tab, item);
     const PhaseItem pi = tab->it[q];
     const RunDesc<FT> &R = runs[pi.slot];
+    if (R.k.nx <= FIELD1_MAX) {
+      const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      const int c = (item - pi.begin) * (FIELD_WG / MCHUNK) + w;
+      if (c * MCHUNK < R.k.nx)
+        field_chunk_publish(R.k, R.part, R.Mc, R.ctot, nullptr, c,
+                            L.stage + w * MCHUNK);
+      continue;
+    }
     FieldArgs A{};
     A.in = R.part;
     A.ngy = R.k.ngy;
