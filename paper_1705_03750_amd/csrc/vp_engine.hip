@@ -138,6 +138,7 @@ KP make_kp(const vp_params *p) {
   k.x_max = p->x_max;
   k.Lx = p->x_max - p->x_min;
   k.hL = 0.5 * k.Lx;
+  k.inv_Lx = 1.0 / k.Lx;
   gox_set(k);
   return k;
 }
