@@ -349,7 +349,10 @@ int launch_predict(vp_ctx *c, int drift, int reg) {
   return launch_elem(c, 0, drift, 1, reg, c->cur, -1);
 }
 
-int launch_zero_counts(vp_ctx *c) {
+// The lists empty again after a query outside the stepping loop: with
+// periodic x by this launch, else the query has cleared its counts itself.
+int clear_counts(vp_ctx *c) {
+  if (!c->k.per) return VP_OK;
   ProfScope ps(c, PK_OTHER);
   hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(c->L.nb, 256)), dim3(256), 0,
                      c->stream, c->counts(c->cur), c->L.nb);
@@ -357,11 +360,12 @@ int launch_zero_counts(vp_ctx *c) {
   return VP_OK;
 }
 
-template <typename FT, int MODE>
+// CLR: outside the stepping loop (clear_counts follows).
+template <typename FT, int MODE, bool CLR>
 int launch_recon(vp_ctx *c, void *fout, int *aout, double *rho_out) {
   const KP &k = c->k;
   ProfScope ps(c, PK_RECON);
-  auto kern = k.per ? k_recon<FT, MODE, 1> : k_recon<FT, MODE, 0>;
+  auto kern = k.per ? k_recon<FT, MODE, 1, false> : k_recon<FT, MODE, 0, CLR>;
   hipLaunchKernelGGL(kern, dim3(c->L.nwg_x * c->L.nwg_y),
                      dim3(512), 0, c->stream, k, c->at<double>(c->L.rec),
                      c->at<double>(c->L.qm), c->counts(c->cur),
@@ -421,10 +425,11 @@ int launch_field(vp_ctx *c, const double *in, int from_part, double *rho_out,
 
 // The reconstruction in one of its modes; the density modes are followed
 // by the field pass (a, a', a'', optionally rho).
-template <int MODE>
+template <int MODE, bool CLR = true>
 int recon(vp_ctx *c, void *fout, int *aout, double *rho_out = nullptr) {
-  const int rc = c->mixed() ? launch_recon<float, MODE>(c, fout, aout, rho_out)
-                            : launch_recon<double, MODE>(c, fout, aout, rho_out);
+  const int rc =
+      c->mixed() ? launch_recon<float, MODE, CLR>(c, fout, aout, rho_out)
+                 : launch_recon<double, MODE, CLR>(c, fout, aout, rho_out);
   if (rc || (MODE != MODE_DENSITY && MODE != MODE_DIAG)) return rc;
   return launch_field(c, c->at<double>(c->L.part), 1, rho_out, nullptr,
                       nullptr, nullptr);
@@ -583,7 +588,7 @@ int diag_now(vp_ctx *c, double *h, unsigned long long *ovf, int *flags) {
   int rc;
   if ((rc = launch_predict(c, 0, 1))) return rc;
   if ((rc = recon<MODE_DIAG>(c, nullptr, nullptr))) return rc;
-  if ((rc = launch_zero_counts(c))) return rc;
+  if ((rc = clear_counts(c))) return rc;
   const long long nwg = (long long)c->L.nwg_x * c->L.nwg_y;
   // the chunk totals are free until the next field
   double *gpart = c->at<double>(c->L.ctot);
@@ -618,10 +623,12 @@ int diag_now(vp_ctx *c, double *h, unsigned long long *ovf, int *flags) {
 int emap_now(vp_ctx *c, double *emap) {
   int rc;
   if ((rc = launch_predict(c, 0, 1))) return rc;
-  rc = c->mixed() ? launch_recon<float, MODE_EMAP>(c, nullptr, nullptr, nullptr)
-                  : launch_recon<double, MODE_EMAP>(c, nullptr, nullptr, nullptr);
+  rc = c->mixed()
+           ? launch_recon<float, MODE_EMAP, true>(c, nullptr, nullptr, nullptr)
+           : launch_recon<double, MODE_EMAP, true>(c, nullptr, nullptr,
+                                                   nullptr);
   if (rc) return rc;
-  if ((rc = launch_zero_counts(c))) return rc;
+  if ((rc = clear_counts(c))) return rc;
   hipLaunchKernelGGL(k_emap_max, dim3(1), dim3(1024), 0, c->stream,
                      c->at<double>(c->L.dpart),
                      (long long)c->L.nwg_x * c->L.nwg_y,
@@ -648,11 +655,11 @@ int run_steps(vp_ctx *c, int n) {
   for (int s = 0; s < n; ++s) {
     if (!predicted && (rc = launch_predict(c, 1, self ? 1 : 0))) return rc;
     if (self) {
-      rc = fused ? (c->mixed() ? launch_recon<float, MODE_DENSITY>(
+      rc = fused ? (c->mixed() ? launch_recon<float, MODE_DENSITY, false>(
                                      c, nullptr, nullptr, nullptr)
-                               : launch_recon<double, MODE_DENSITY>(
+                               : launch_recon<double, MODE_DENSITY, false>(
                                      c, nullptr, nullptr, nullptr))
-                 : recon<MODE_DENSITY>(c, nullptr, nullptr);
+                 : recon<MODE_DENSITY, false>(c, nullptr, nullptr);
       if (rc) return rc;
     }
     c->step += 1;
@@ -993,7 +1000,7 @@ int vp_reconstruct_f(vp_ctx *c, int scheme, void *f_out_dev) {
                     : launch_remap_t<double, 1>(c, f_out_dev);
   }
   if (rc) return rc;
-  return launch_zero_counts(c);
+  return clear_counts(c);
 }
 
 int vp_density(vp_ctx *c, double *rho_out_dev) {
@@ -1002,7 +1009,7 @@ int vp_density(vp_ctx *c, double *rho_out_dev) {
   int rc;
   if ((rc = launch_predict(c, 0, 1))) return rc;
   if ((rc = recon<MODE_DENSITY>(c, nullptr, nullptr, rho_out_dev))) return rc;
-  return launch_zero_counts(c);
+  return clear_counts(c);
 }
 
 int vp_poisson(vp_ctx *c, const double *rho, double *a, double *da,
@@ -1057,7 +1064,7 @@ int vp_get_assignment(vp_ctx *c, int32_t *assign) {
   int rc;
   if ((rc = launch_predict(c, 0, 1))) return rc;
   if ((rc = recon<MODE_ASSIGN>(c, nullptr, assign))) return rc;
-  return launch_zero_counts(c);
+  return clear_counts(c);
 }
 
 int vp_time(vp_ctx *c, double *t, int64_t *step) {

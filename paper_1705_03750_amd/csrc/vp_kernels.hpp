@@ -1892,7 +1892,13 @@ __device__ __forceinline__ int lattice_col(const KP &p, int k, double &shift) {
 // partials of its row group (the strips in order); the field adds the
 // groups in increasing order.  No workgroup waits on another, so the
 // launch needs no device-scope synchronisation.
-template <typename FT, int MODE, int PER, bool BF = false>
+//
+// CLR: the wavefront also clears its block's count, so that a query outside
+// the stepping loop leaves the lists empty without a launch of its own (5 us;
+// (an output time at 2048^2 with four of them, FP64: 423 -> 417 us).  Not with
+// periodic x, where two
+// wavefronts share the seam's lists.
+template <typename FT, int MODE, int PER, bool BF = false, bool CLR = false>
 __device__ __forceinline__ void recon_tile(
     KP p, const double *__restrict__ rec, const double *__restrict__ qm,
     const int *__restrict__ cnt,
@@ -1924,6 +1930,7 @@ __device__ __forceinline__ void recon_tile(
     double dqx, dqv;
     best = query_block<PER, BF>(p, rec, L, id0, n, scan_all, xP, vP, dqx,
                                 dqv, qstage[w]);
+    if (CLR && lane == 0) const_cast<int *>(cnt)[b] = 0;
     if (live && best >= 0) {
       const double Qx = qm[2 * (size_t)best] + dqx;
       const double Qv = qm[2 * (size_t)best + 1] + dqv;
@@ -2034,7 +2041,7 @@ __device__ __forceinline__ void recon_tile(
   }
 }
 
-template <typename FT, int MODE, int PER>
+template <typename FT, int MODE, int PER, bool CLR>
 __global__ __launch_bounds__(512) void k_recon(
     KP p, const double *__restrict__ rec, const double *__restrict__ qm,
     const int *__restrict__ cnt,
@@ -2048,8 +2055,8 @@ __global__ __launch_bounds__(512) void k_recon(
   clock_tau(p);
   // branch-free candidates (as many registers as it takes; the batched
   // kernel, held to 64, keeps the masked form)
-  recon_tile<FT, MODE, PER, true>(p, rec, qm, cnt, lst, flags, F, part, fout,
-                                  aout, dpart, ovf, bx, gy);
+  recon_tile<FT, MODE, PER, true, CLR>(p, rec, qm, cnt, lst, flags, F, part,
+                                       fout, aout, dpart, ovf, bx, gy);
 }
 
 // Resampling value at every site (section 2.3.2): nearest element, the
@@ -2082,6 +2089,8 @@ __device__ __forceinline__ void remap_tile(
   double dqx, dqv;
   const int best = query_block<PER>(p, rec, L, id0, n, scan_all, xP, vP, dqx,
                                     dqv, qstage[w]);
+  // into f_out: a query outside the stepping loop, see recon_tile's CLR
+  if (TO_F && !PER && lane == 0) const_cast<int *>(cnt)[b] = 0;
   if (!live) return;
   FT val = (FT)0;
   // zero edge rows (and columns, unless x is periodic)
