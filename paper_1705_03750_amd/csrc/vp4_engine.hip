@@ -246,6 +246,13 @@ int field_from(vp4_ctx *c, const double *part, double *rho) {
   double *re = c->at<double>(c->L.re), *im = c->at<double>(c->L.im);
   double *tr = c->at<double>(c->L.tr), *ti = c->at<double>(c->L.ti);
   const unsigned row = k.ns * sizeof(double);
+  if (k.ns <= FS_MAX) {
+    hipLaunchKernelGGL(k4_field_small, dim3(1), dim3(FS_WG),
+                       (2 + 8 * k.ns) * row, c->stream, k, part, rho, tw,
+                       c->at<double>(c->L.fld));
+    VP4_CHECK(c, "k4_field_small");
+    return VP4_OK;
+  }
   hipLaunchKernelGGL(k4_rho_dft_x, dim3(k.ns), dim3(FT_WG), 3 * row, c->stream,
                      k, part, rho, tw, re, im);
   hipLaunchKernelGGL(k4_spectrum_y, dim3(k.ns), dim3(FT_WG), 8 * row,

@@ -1290,6 +1290,49 @@ __global__ __launch_bounds__(FT_WG) void k4_rho_dft_x(
   }
 }
 
+// Spectra of a_x and a_y from rho^ = (sr, si) at wave numbers (pf, qy): phi^ =
+// -2 G rho^ / |k|^2, a^ = -i k phi^ (k = 0 and the Nyquist derivative zero).
+__device__ __forceinline__ void force_spectrum(const KP &p, int pf, int qy,
+                                               double sr, double si,
+                                               double r[2], double i[2]) {
+  const int n = p.ns;
+  const double twopi = 6.283185307179586476925286766559;
+  const int half = (n % 2 == 0) ? n / 2 - 1 : n / 2;
+  const int pp = (pf <= half) ? pf : pf - n, qq = (qy <= half) ? qy : qy - n;
+  const double kx = twopi * (double)pp / p.L, ky = twopi * (double)qq / p.L;
+  const double k2 = kx * kx + ky * ky;
+  const double gk = (-2.0 * p.G) / k2;
+  const double pr = gk * sr, pi = gk * si;
+#pragma unroll
+  for (int comp = 0; comp < 2; ++comp) {
+    double kd = comp == 0 ? kx : ky;
+    if ((comp == 0 ? pf : qy) * 2 == n) kd = 0.0;
+    const bool mean = pf == 0 && qy == 0;
+    r[comp] = mean ? 0.0 : kd * pi;
+    i[comp] = mean ? 0.0 : -(kd * pr);
+  }
+}
+
+// Fields of component c at site q = (i, j) of n2: 0 and 1 = a_x and a_y, 2-5 =
+// d a_x/dx, d a_x/dy, d a_y/dx, d a_y/dy, 6-8 = a_x,xx a_x,xy a_x,yy, 9-11 the
+// same of a_y, by centred differences of the rows j - 1, j and j + 1.
+__device__ __forceinline__ void force_fields(const KP &p, int c, int i,
+                                             size_t q, size_t n2,
+                                             const double *lo,
+                                             const double *mid,
+                                             const double *hi,
+                                             double *__restrict__ fld) {
+  const int ip = i + 1 < p.ns ? i + 1 : 0, im = i > 0 ? i - 1 : p.ns - 1;
+  const double dx = p.dx;
+  fld[c * n2 + q] = mid[i];
+  fld[(2 + 2 * c) * n2 + q] = (mid[ip] - mid[im]) / (2.0 * dx);
+  fld[(3 + 2 * c) * n2 + q] = (hi[i] - lo[i]) / (2.0 * dx);
+  fld[(6 + 3 * c) * n2 + q] = ((mid[ip] + mid[im]) - 2.0 * mid[i]) / (dx * dx);
+  fld[(7 + 3 * c) * n2 + q] =
+      (((hi[ip] - lo[ip]) - hi[im]) + lo[im]) / (4.0 * (dx * dx));
+  fld[(8 + 3 * c) * n2 + q] = ((hi[i] + lo[i]) - 2.0 * mid[i]) / (dx * dx);
+}
+
 // Column pf = blockIdx.x: R2[q][pf] = sum_j R1[j][pf] e^{-2 pi i q j / ns};
 // the spectra of a_x and a_y, phi^ = -2 G rho^ / |k|^2, a^ = -i k phi^ (k = 0
 // and the Nyquist derivative zero); back along y, T[c][j][pf] = sum_q
@@ -1308,8 +1351,6 @@ __global__ __launch_bounds__(FT_WG) void k4_spectrum_y(
     ri[j] = im[(size_t)j * n + pf];
   }
   __syncthreads();
-  const double twopi = 6.283185307179586476925286766559;
-  const int half = (n % 2 == 0) ? n / 2 - 1 : n / 2;
   for (int qy = threadIdx.x; qy < n; qy += FT_WG) {
     double sr = 0.0, si = 0.0;
     int m = 0;
@@ -1320,18 +1361,12 @@ __global__ __launch_bounds__(FT_WG) void k4_spectrum_y(
       m += qy;
       m -= m >= n ? n : 0;
     }
-    const int pp = (pf <= half) ? pf : pf - n, qq = (qy <= half) ? qy : qy - n;
-    const double kx = twopi * (double)pp / p.L, ky = twopi * (double)qq / p.L;
-    const double k2 = kx * kx + ky * ky;
-    const double gk = (-2.0 * p.G) / k2;
-    const double pr = gk * sr, pi = gk * si;
+    double r[2], i[2];
+    force_spectrum(p, pf, qy, sr, si, r, i);
 #pragma unroll
     for (int comp = 0; comp < 2; ++comp) {
-      double kd = comp == 0 ? kx : ky;
-      if ((comp == 0 ? pf : qy) * 2 == n) kd = 0.0;
-      const bool mean = pf == 0 && qy == 0;
-      ar[comp * n + qy] = mean ? 0.0 : kd * pi;
-      ai[comp * n + qy] = mean ? 0.0 : -(kd * pr);
+      ar[comp * n + qy] = r[comp];
+      ai[comp * n + qy] = i[comp];
     }
   }
   __syncthreads();
@@ -1353,9 +1388,7 @@ __global__ __launch_bounds__(FT_WG) void k4_spectrum_y(
 }
 
 // Row j = blockIdx.x: the inverse along x, real part / ns^2, of rows j - 1, j
-// and j + 1 (fields 0, a_x, and 1, a_y, of row j written), then the centred
-// differences of row j: fields 2-5 = d a_x/dx, d a_x/dy, d a_y/dx, d a_y/dy;
-// 6-8 = a_x,xx a_x,xy a_x,yy; 9-11 the same of a_y.
+// and j + 1, then the fields of row j.
 __global__ __launch_bounds__(FT_WG) void k4_force_x(KP p,
                                                     const double *__restrict__ tr,
                                                     const double *__restrict__ ti,
@@ -1383,22 +1416,128 @@ __global__ __launch_bounds__(FT_WG) void k4_force_x(KP p,
     a6[o] = sr * (1.0 / ((double)n * (double)n));
   }
   __syncthreads();
-  const double dx = p.dx;
   for (int o = threadIdx.x; o < 2 * n; o += FT_WG) {
     const int c = o / n, i = o - c * n;
-    const int ip = i + 1 < n ? i + 1 : 0, im = i > 0 ? i - 1 : n - 1;
     const double *A = a6 + c * 3 * n;  // row r of the three at A + r n
-    auto at = [&](int ii, int r) { return A[r * n + ii]; };
-    const size_t q = (size_t)j * n + i;
-    fld[c * n2 + q] = at(i, 1);
-    fld[(2 + 2 * c) * n2 + q] = (at(ip, 1) - at(im, 1)) / (2.0 * dx);
-    fld[(3 + 2 * c) * n2 + q] = (at(i, 2) - at(i, 0)) / (2.0 * dx);
-    fld[(6 + 3 * c) * n2 + q] =
-        ((at(ip, 1) + at(im, 1)) - 2.0 * at(i, 1)) / (dx * dx);
-    fld[(7 + 3 * c) * n2 + q] =
-        (((at(ip, 2) - at(ip, 0)) - at(im, 2)) + at(im, 0)) / (4.0 * (dx * dx));
-    fld[(8 + 3 * c) * n2 + q] =
-        ((at(i, 2) + at(i, 0)) - 2.0 * at(i, 1)) / (dx * dx);
+    force_fields(p, c, i, (size_t)j * n + i, n2, A, A + n, A + 2 * n, fld);
+  }
+}
+
+// The whole field in one workgroup, every transform in LDS, for grids of at
+// most FS_MAX sites per axis, by the operations of the three launches in their
+// order.  Bound by the round trip of the partials and the chains of the sums;
+// the work grows as ns^3 on one compute unit while the three launches cost
+// about 14 us whatever the size.  us per step, three launches / one: 8 sites
+// (12 per velocity axis) 12.4 / 8.3, 12 13.8 / 10.5, 16 (16) 14.1 / 11.4, 16
+// (40) 17.0 / 15.9, 20 (12) 14.8 / 16.9, 24 15.1 / 20.8.
+constexpr int FS_MAX = 16;
+constexpr int FS_WG = 512;
+
+__global__ __launch_bounds__(FS_WG) void k4_field_small(
+    KP p, const double *__restrict__ part, double *__restrict__ rho,
+    const double *__restrict__ tw, double *__restrict__ fld) {
+  extern __shared__ double ft[];  // 2 ns + 8 ns^2 doubles
+  const int n = p.ns, n2 = n * n, tid = threadIdx.x;
+  double *cs = ft, *sn = cs + n, *X = sn + n, *Y = X + 4 * n2;
+  for (int i = tid; i < 2 * n; i += FS_WG) cs[i] = tw[i];
+  for (int q = tid; q < n2; q += FS_WG) {
+    if (part) {
+      const int nvb = p.nb[2] * p.nb[3];
+      double s = 0.0;
+      for (int v0 = 0; v0 < nvb; v0 += 32) {
+        double x[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u)
+          x[u] = v0 + u < nvb ? part[(size_t)(v0 + u) * n2 + q] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 32; ++u)
+          if (v0 + u < nvb) s += x[u];
+      }
+      Y[q] = (p.du * p.du) * s;
+      rho[q] = Y[q];
+    } else {
+      Y[q] = rho[q];
+    }
+  }
+  __syncthreads();
+  // along x: X = R1[j][pf], real and imaginary
+  for (int o = tid; o < n2; o += FS_WG) {
+    const int j = o / n, pf = o - j * n;
+    double sr = 0.0, si = 0.0;
+    int m = 0;
+#pragma unroll 8
+    for (int i = 0; i < n; ++i) {
+      const double v = Y[j * n + i];
+      sr = fma(v, cs[m], sr);
+      si = fma(-v, sn[m], si);
+      m += pf;
+      m -= m >= n ? n : 0;
+    }
+    X[o] = sr;
+    X[n2 + o] = si;
+  }
+  __syncthreads();
+  // along y and the spectra: Y = a^[comp][real, imaginary][qy][pf]
+  for (int o = tid; o < n2; o += FS_WG) {
+    const int qy = o / n, pf = o - qy * n;
+    double sr = 0.0, si = 0.0;
+    int m = 0;
+#pragma unroll 8
+    for (int j = 0; j < n; ++j) {
+      const double a = X[j * n + pf], b = X[n2 + j * n + pf];
+      sr = fma(a, cs[m], fma(b, sn[m], sr));
+      si = fma(b, cs[m], fma(-a, sn[m], si));
+      m += qy;
+      m -= m >= n ? n : 0;
+    }
+    double r[2], i[2];
+    force_spectrum(p, pf, qy, sr, si, r, i);
+#pragma unroll
+    for (int comp = 0; comp < 2; ++comp) {
+      Y[2 * comp * n2 + o] = r[comp];
+      Y[(2 * comp + 1) * n2 + o] = i[comp];
+    }
+  }
+  __syncthreads();
+  // back along y: X = T[comp][real, imaginary][j][pf]
+  for (int o = tid; o < 2 * n2; o += FS_WG) {
+    const int comp = o / n2, g = o - comp * n2, j = g / n, pf = g - j * n;
+    const double *A = Y + 2 * comp * n2 + pf;
+    double sr = 0.0, si = 0.0;
+    int m = 0;
+#pragma unroll 8
+    for (int qy = 0; qy < n; ++qy) {
+      const double a = A[qy * n], b = A[n2 + qy * n];
+      sr = fma(a, cs[m], fma(-b, sn[m], sr));
+      si = fma(b, cs[m], fma(a, sn[m], si));
+      m += j;
+      m -= m >= n ? n : 0;
+    }
+    X[2 * comp * n2 + g] = sr;
+    X[(2 * comp + 1) * n2 + g] = si;
+  }
+  __syncthreads();
+  // back along x: Y = a[comp][j][i]
+  for (int o = tid; o < 2 * n2; o += FS_WG) {
+    const int comp = o / n2, g = o - comp * n2, j = g / n, i = g - j * n;
+    const double *T = X + 2 * comp * n2 + j * n;
+    double sr = 0.0;
+    int m = 0;
+#pragma unroll 8
+    for (int pf = 0; pf < n; ++pf) {
+      sr = fma(T[pf], cs[m], fma(-T[n2 + pf], sn[m], sr));
+      m += i;
+      m -= m >= n ? n : 0;
+    }
+    Y[o] = sr * (1.0 / ((double)n * (double)n));
+  }
+  __syncthreads();
+  for (int o = tid; o < 2 * n2; o += FS_WG) {
+    const int c = o / n2, g = o - c * n2, j = g / n, i = g - j * n;
+    const double *A = Y + c * n2;
+    const int jm = j > 0 ? j - 1 : n - 1, jp = j + 1 < n ? j + 1 : 0;
+    force_fields(p, c, i, (size_t)g, (size_t)n2, A + jm * n, A + j * n,
+                 A + jp * n, fld);
   }
 }
 

@@ -1894,10 +1894,9 @@ __device__ __forceinline__ int lattice_col(const KP &p, int k, double &shift) {
 // launch needs no device-scope synchronisation.
 //
 // CLR: the wavefront also clears its block's count, so that a query outside
-// the stepping loop leaves the lists empty without a launch of its own (5 us;
-// (an output time at 2048^2 with four of them, FP64: 423 -> 417 us).  Not with
-// periodic x, where two
-// wavefronts share the seam's lists.
+// the stepping loop leaves the lists empty without a launch of its own (an
+// output time at 2048^2 with four of them, FP64: 423 -> 417 us).  Not with
+// periodic x, where two wavefronts share the seam's lists.
 template <typename FT, int MODE, int PER, bool BF = false, bool CLR = false>
 __device__ __forceinline__ void recon_tile(
     KP p, const double *__restrict__ rec, const double *__restrict__ qm,
