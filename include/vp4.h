@@ -123,9 +123,9 @@ int vp4_set_elements(vp4_ctx *ctx, const double *el_dev);
 int vp4_get_assignment(vp4_ctx *ctx, int32_t *assign_dev);
 
 /* Profiling: per kernel kind (0 predict + lists, 1 reconstruction, 2 field,
- * 3 kick, 4 remap evaluation, 5 spline fit, 6 other) summed milliseconds and
- * launch counts between vp4_prof_begin and vp4_prof_end (HIP events on the
- * context's stream). */
+ * 3 kick and the next predictor, 4 remap evaluation, 5 spline fit, 6 other)
+ * summed milliseconds and launch counts between vp4_prof_begin and
+ * vp4_prof_end (HIP events on the context's stream). */
 #define VP4_PROF_KINDS 7
 int vp4_prof_begin(vp4_ctx *ctx, int max_launches);
 int vp4_prof_end(vp4_ctx *ctx, double *ms_host, int64_t *n_host);
