@@ -420,16 +420,24 @@ __global__ __launch_bounds__(256) void k4_elem(
     const double X = S.s[S_P + a][e];
     const double c = (a < 2 ? X : X + p.vmax) * inv_d - 0.5;
     int lo = (int)ceil(c - rs), hi = (int)floor(c + rs);
+    bool far = false;
     if (a >= 2) {
       lo = max(lo, 0);
       hi = min(hi, p.nv - 1);
     } else {
-      // nearest images lie within half a period; a window reaching further
-      // enters every list column (the seam's twice: a harmless repetition)
-      lo = max(lo, (int)floor(c) - p.ns / 2);
-      hi = min(hi, (int)ceil(c) + p.ns / 2);
+      // images lie within half a period of an element at most half a period
+      // off the square; a window reaching further enters every list column
+      // (the seam's twice: a harmless repetition).  Of an element further off
+      // a site sees an image beyond half a period (one period is taken off),
+      // which such a window may reach: not listed
+      const int reach_lo = (int)floor(c) - p.ns / 2;
+      const int reach_hi = (int)ceil(c) + p.ns / 2;
+      far = (lo < reach_lo || hi > reach_hi) && !(fabs(X - p.hL) <= p.L);
+      lo = max(lo, reach_lo);
+      hi = min(hi, reach_hi);
     }
-    const int b0 = blk_of(p, a, lo), n = blk_of(p, a, hi) - b0 + 1;
+    const int b0 = blk_of(p, a, lo);
+    const int n = far ? SPAN + 1 : blk_of(p, a, hi) - b0 + 1;
     S.blo[a][e] = b0;  // unwrapped on x and y
     S.ext[a][e] = n;
     // the blocks of the element's box: none for a bad element or a window
