@@ -24,6 +24,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace vpk {
 
 constexpr int PX = 16;  // x padding of F / C (values)
@@ -885,6 +887,20 @@ __device__ __forceinline__ void stage_wait() {
 template <typename T>
 __device__ __forceinline__ T uload(const T *q) {
   return *(const __attribute__((address_space(4))) T *)q;
+}
+
+// The count of a block's list.  A query that clears the counts it has read
+// (CLR) reads them by an ordinary load: uload tells the compiler that nothing
+// writes there, so it may move such a load past the store.
+template <bool CLR>
+using CountPtr = std::conditional_t<CLR, int, const int> *;
+
+template <bool CLR>
+__device__ __forceinline__ int block_count(CountPtr<CLR> q) {
+  if constexpr (CLR)
+    return __builtin_amdgcn_readfirstlane(*q);
+  else
+    return uload(q);
 }
 
 // The candidates of one staged round, unrolled: the record offsets are
@@ -1904,7 +1920,7 @@ __device__ __forceinline__ int lattice_col(const KP &p, int k, double &shift) {
 template <typename FT, int MODE, int PER, bool BF = false, bool CLR = false>
 __device__ __forceinline__ void recon_tile(
     KP p, const double *__restrict__ rec, const double *__restrict__ qm,
-    const int *__restrict__ cnt,
+    CountPtr<CLR> __restrict__ cnt,
     const int *__restrict__ lst, const int *__restrict__ flags,
     const FT *__restrict__ F, double *__restrict__ part, FT *__restrict__ fout,
     int *__restrict__ aout, double *__restrict__ dpart,
@@ -1926,14 +1942,16 @@ __device__ __forceinline__ void recon_tile(
     const int b = bv * p.nbx + (PER ? list_bx(p, bx) : bx);
     const int *L = lst + (size_t)b * p.cap;
     const int id0 = list_head(p, L);
-    const int n = uload(cnt + b);
+    const int n = block_count<CLR>(cnt + b);
     const bool scan_all = (n > p.cap) || (uload(flags) & FLAG_WIDE);
     if (scan_all && lane == 0 && n > p.cap) atomicAdd(ovf, 1ull);
     const double xP = site_x(p, i), vP = site_v(p, j);
     double dqx, dqv;
     best = query_block<PER, BF>(p, rec, L, id0, n, scan_all, xP, vP, dqx,
                                 dqv, qstage[w]);
-    if (CLR && lane == 0) const_cast<int *>(cnt)[b] = 0;
+    if constexpr (CLR) {
+      if (lane == 0) cnt[b] = 0;
+    }
     if (live && best >= 0) {
       const double Qx = qm[2 * (size_t)best] + dqx;
       const double Qv = qm[2 * (size_t)best + 1] + dqv;
@@ -2047,7 +2065,7 @@ __device__ __forceinline__ void recon_tile(
 template <typename FT, int MODE, int PER, bool CLR>
 __global__ __launch_bounds__(512) void k_recon(
     KP p, const double *__restrict__ rec, const double *__restrict__ qm,
-    const int *__restrict__ cnt,
+    int *__restrict__ cnt,
     const int *__restrict__ lst, const int *__restrict__ flags,
     const FT *__restrict__ F, double *__restrict__ part, FT *__restrict__ fout,
     int *__restrict__ aout, double *__restrict__ dpart,
@@ -2066,11 +2084,12 @@ __global__ __launch_bounds__(512) void k_recon(
 // beta-restricted neighbour set (diagonals dropped when an axis needs three
 // values), W(2d)-weighted blend of their predictions Q_r, cubic B-spline of
 // F_ini at Q_r; the outermost ring is zero.  Writes F (padded interior)
-// when TO_F == 0, else f_out.
-template <typename FT, int TO_F, int PER>
+// when TO_F == 0, else f_out (a query outside the stepping loop: clears its
+// counts as recon_tile does with CLR).
+template <typename FT, int TO_F, int PER, bool CLR = TO_F && !PER>
 __device__ __forceinline__ void remap_tile(
     KP p, const double *__restrict__ rec, const double *__restrict__ qm,
-    const int *__restrict__ cnt,
+    CountPtr<CLR> __restrict__ cnt,
     const int *__restrict__ lst, const int *__restrict__ flags,
     const FT *__restrict__ C, FT *__restrict__ Fout,
     unsigned long long *__restrict__ ovf, const int bx, const int gy) {
@@ -2085,15 +2104,16 @@ __device__ __forceinline__ void remap_tile(
   const int b = bv * p.nbx + (PER ? list_bx(p, bx) : bx);
   const int *L = lst + (size_t)b * p.cap;
   const int id0 = list_head(p, L);
-  const int n = uload(cnt + b);
+  const int n = block_count<CLR>(cnt + b);
   const bool scan_all = (n > p.cap) || (uload(flags) & FLAG_WIDE);
   if (scan_all && lane == 0 && n > p.cap) atomicAdd(ovf, 1ull);
   const double xP = site_x(p, i), vP = site_v(p, j);
   double dqx, dqv;
   const int best = query_block<PER>(p, rec, L, id0, n, scan_all, xP, vP, dqx,
                                     dqv, qstage[w]);
-  // into f_out: a query outside the stepping loop, see recon_tile's CLR
-  if (TO_F && !PER && lane == 0) const_cast<int *>(cnt)[b] = 0;
+  if constexpr (CLR) {
+    if (lane == 0) cnt[b] = 0;
+  }
   if (!live) return;
   FT val = (FT)0;
   // zero edge rows (and columns, unless x is periodic)
@@ -2161,7 +2181,7 @@ __device__ __forceinline__ void remap_tile(
 template <typename FT, int TO_F, int PER>
 __global__ __launch_bounds__(512) void k_remap_eval(
     KP p, const double *__restrict__ rec, const double *__restrict__ qm,
-    const int *__restrict__ cnt,
+    int *__restrict__ cnt,
     const int *__restrict__ lst, const int *__restrict__ flags,
     const FT *__restrict__ C, FT *__restrict__ Fout,
     unsigned long long *__restrict__ ovf) {
