@@ -69,6 +69,7 @@ KP make_kp(const vp4_params *p) {
   k.inv_ms = 1.0 / k.ms;
   k.inv_mv = 1.0 / k.mv;
   k.cap = list_cap(p->ss, p->sv);
+  k.direct = k.ms <= 2 && k.E <= DIRECT_MAX;
   k.L = p->L;
   k.hL = 0.5 * p->L;
   k.vmax = p->vmax;
@@ -189,6 +190,7 @@ unsigned grid_for(long long n, int bs) {
 }
 
 int zero_counts(vp4_ctx *c) {
+  if (c->k.direct) return VP4_OK;  // never counted in
   hipLaunchKernelGGL(k4_zero, dim3(grid_for(std::min<long long>(c->L.nl, 1 << 22), 256)),
                      dim3(256), 0, c->stream, c->counts(c->cur), c->L.nl);
   VP4_CHECK(c, "k4_zero");
@@ -200,11 +202,12 @@ int zero_counts(vp4_ctx *c) {
 int launch_elem(vp4_ctx *c, int kick, int drift, int predict, int reg_buf,
                 int zero_buf) {
   Prof ps(c, kick ? PK_KICK : PK_PREDICT);
+  const bool clear = zero_buf >= 0 && !c->k.direct;
   hipLaunchKernelGGL(k4_elem, dim3(grid_for(c->k.E, EPW)), dim3(256), 0,
                      c->stream, c->k, c->at<double>(c->L.st),
                      c->at<double>(c->L.fld), c->at<double>(c->L.rec),
-                     zero_buf >= 0 ? c->counts(zero_buf) : nullptr,
-                     zero_buf >= 0 ? c->L.nl : 0, c->counts(reg_buf),
+                     clear ? c->counts(zero_buf) : nullptr,
+                     clear ? c->L.nl : 0, c->counts(reg_buf),
                      c->at<int>(c->L.lst), c->at<int>(c->L.flags), kick, drift,
                      predict);
   VP4_CHECK(c, "k4_elem");

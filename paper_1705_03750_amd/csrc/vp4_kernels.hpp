@@ -36,6 +36,14 @@ constexpr int RS = 64;                     // record doubles (512 bytes)
 constexpr int R_A = 4, R_K = 20, R_DELTA = 21, R_G = 24;  // record offsets
 constexpr int BLK = 4;                     // sites per axis of a block
 constexpr int SPAN = 4096;                 // max blocks of one element
+// Grids without lists: at most DIRECT_MAX elements, at most two per ring (a
+// window of the undeformed lattice then covers the ring already, so that lists
+// hold every element, most of them more than once, and a workgroup or two
+// make all the claims).  us for f (list / none): 8^4, stride 4, 16 elements 46 /
+// 29; 16^4, stride 8 61 / 29; 32^4, stride 16 354 / 92; 16^4, strides 8 and 4,
+// 64 elements 74 / 59.  With three per ring (24^2 x 8^2) 45 / 41, and f by the
+// spline 71 / 64, but a step 79 / 66; with 144 elements (8^2 x 24^2) 77 / 109.
+constexpr int DIRECT_MAX = 64;
 enum { FL_NUMERIC = 1, FL_WIDE = 2 };
 enum { M_DENSITY = 0, M_F = 1, M_ASSIGN = 2 };
 
@@ -50,6 +58,7 @@ struct KP {
   int nb[4];     // blocks per axis
   int nls;       // list columns per space axis (ns / 4)
   int cap;       // list slots per block
+  int direct;    // no lists, queries scan the elements (DIRECT_MAX)
   double L, hL, vmax, dx, du, inv_dx, inv_du, G, dt, h, beta;
   double inv_ms, inv_mv;  // 1 / ms, 1 / mv (lat_index)
   double Dm[4], rD[4];  // element spacings and their inverses; the two space
@@ -437,7 +446,7 @@ __global__ __launch_bounds__(256) void k4_elem(
       hi = min(hi, reach_hi);
     }
     const int b0 = blk_of(p, a, lo);
-    const int n = far ? SPAN + 1 : blk_of(p, a, hi) - b0 + 1;
+    const int n = far || p.direct ? SPAN + 1 : blk_of(p, a, hi) - b0 + 1;
     S.blo[a][e] = b0;  // unwrapped on x and y
     S.ext[a][e] = n;
     // the blocks of the element's box: none for a bad element or a window
@@ -776,7 +785,7 @@ __device__ __forceinline__ bool reaches(const KP &p, const double *r,
 // read through the scalar cache: they are uniform over the wavefront, and
 // the operands come straight from scalar registers.
 //
-// With an overflowed list, or a too-wide element, every element is
+// With an overflowed list, a too-wide element or no lists every element is
 // scanned.  SORTED: a wavefront first tests 64 of them at a time against its
 // sub-block (reaches) and walks those that pass; else it walks them all, each
 // record waited for.  4096 elements at 256^2 x 4^2 (stride 4), walked: 29.0 ms
