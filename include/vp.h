@@ -267,8 +267,9 @@ int vp_prof_end(vp_ctx *ctx, double *ms_host, int64_t *n_host);
  * is admitted (FIFO) as soon as a run slot is free and its vp_footprint fits
  * in the unused part of the server's device pool; its state (F_ini, spline,
  * elements) stays resident until it completes.  Every tick advances all
- * admitted runs by one step with one fixed sequence of batched launches
- * (captured once as a HIP graph and replayed); a run's arithmetic is the
+ * admitted runs by one step with batched launches: the replay of a HIP graph
+ * (reconstruction, field, kick) where no run starts, resamples or finishes,
+ * else the phases that have work, one by one; a run's arithmetic is the
  * same as a run alone (vp_step, then vp_reconstruct_f with the transport
  * scheme), so its output is bitwise the same alone or in any mix. */
 typedef struct vp_server vp_server;
@@ -296,7 +297,8 @@ typedef struct vp_server_stats {
   double gpu_busy_s;    /* device time of all ticks (HIP events) */
   int64_t ticks, site_updates, admitted, completed;
   int32_t max_active;   /* most runs resident at once */
-  int32_t graph_replay; /* 1 when ticks ran as HIP graph replays */
+  int32_t graph_replay; /* 1 when the server holds the HIP graph (0: capture
+                           was refused, every tick is launched one by one) */
 } vp_server_stats;
 
 /* Device bytes the server keeps at the head of its pool for run and work

@@ -38,11 +38,12 @@ constexpr int BLK = 4;                     // sites per axis of a block
 constexpr int SPAN = 4096;                 // max blocks of one element
 // Grids without lists: at most DIRECT_MAX elements, at most two per ring (a
 // window of the undeformed lattice then covers the ring already, so that lists
-// hold every element, most of them more than once, and a workgroup or two
-// make all the claims).  us for f (list / none): 8^4, stride 4, 16 elements 46 /
-// 29; 16^4, stride 8 61 / 29; 32^4, stride 16 354 / 92; 16^4, strides 8 and 4,
-// 64 elements 74 / 59.  With three per ring (24^2 x 8^2) 45 / 41, and f by the
-// spline 71 / 64, but a step 79 / 66; with 144 elements (8^2 x 24^2) 77 / 109.
+// hold every element, most of them more than once, and one to four workgroups
+// make all the claims).  us for f with lists / without: 8^4, stride 4, 16
+// elements 46 / 31; 16^4, stride 8 61 / 28; 32^4, stride 16 354 / 92; 16^4,
+// strides 8 and 4, 64 elements 74 / 59.  Above: three per ring (24^2 x 8^2) 45 /
+// 41, but a step 66 with lists and 79 with the scan they replaced; 144 elements
+// (8^2 x 24^2) 77 / 109.
 constexpr int DIRECT_MAX = 64;
 enum { FL_NUMERIC = 1, FL_WIDE = 2 };
 enum { M_DENSITY = 0, M_F = 1, M_ASSIGN = 2 };
@@ -781,9 +782,9 @@ __device__ __forceinline__ bool reaches(const KP &p, const double *r,
 // thread (query_filter); each wavefront then walks its own sub-block's
 // candidates, the near ones (centre closer than one spacing, about the
 // undeformed lattice's nearest few) first, so that the far ones can be
-// dropped by their distance bound (a lane per candidate) and by the cull.  Records are
-// read through the scalar cache: they are uniform over the wavefront, and
-// the operands come straight from scalar registers.
+// dropped by their distance bound (a lane per candidate) and by the cull.
+// Records are read through the scalar cache: they are uniform over the
+// wavefront, and the operands come straight from scalar registers.
 //
 // With an overflowed list, a too-wide element or no lists every element is
 // scanned.  SORTED: a wavefront first tests 64 of them at a time against its

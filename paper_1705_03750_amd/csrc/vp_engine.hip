@@ -329,7 +329,8 @@ int launch_elem_field(vp_ctx *c, int predict, int reg, int reg_buf,
                   : (k.per ? k_elem_window<false, true>
                            : k_elem_window<false, false>);
   hipLaunchKernelGGL(kern, dim3(elem_patches(k.mx, k.mv)), dim3(ELEMC_WG), 0,
-                     c->stream, k, part, Mc, ctot, cmax, st, rec, qm, cz, nb, cr, lst, flags, predict, reg);
+                     c->stream, k, part, Mc, ctot, cmax, st, rec, qm, cz, nb,
+                     cr, lst, flags, predict, reg);
   VP_LAUNCH_CHECK(c, "k_elem_window");
   return VP_OK;
 }

@@ -612,14 +612,6 @@ __device__ __forceinline__ void reg_table(const KP &p, const RegBox &B,
   if (B.n > RB) reg_direct(p, B, RB, e, cnt, lst);
 }
 
-__device__ __forceinline__ void elem_record(
-    const KP &p, const ElemState &s, int e, double *__restrict__ rec,
-    double *__restrict__ qm, int *__restrict__ cnt, int *__restrict__ lst,
-    int *__restrict__ flags, int reg) {
-  const RegBox B = elem_record_box(p, s, e, rec, qm, flags, reg);
-  if (B.n > 0) reg_direct(p, B, 0, e, cnt, lst);
-}
-
 // TAB false: thread gid takes element gid and registers every claim with
 // its own device atomic (reg_direct).  TAB true: workgroup w takes lattice
 // patch w and registers the first TABLE_RB blocks of each box through the
