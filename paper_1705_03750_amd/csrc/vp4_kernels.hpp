@@ -1145,7 +1145,7 @@ __device__ __forceinline__ void index_pos(const KP &p, const double Q[4],
 // Bound by FP64 vector instructions.  A block's list holds 69 to 81 elements
 // of which a site needs one; sorting the list per sub-block, culling, reading
 // records as scalar operands and the 15-value interpolation took a wavefront
-// from 8500 vector instructions to about 3000 and a launch at 64^4 (mixed,
+// from 8500 vector instructions to 2200 and a launch at 64^4 (mixed,
 // stride 4) from 5650 to 1720 us; at 16^4, where every element used to be
 // scanned, from 156 to 31 us.  Six wavefronts per SIMD (80 VGPRs, the spills
 // outside the candidate loop) against the 4 the compiler takes by itself and
