@@ -69,7 +69,7 @@ KP make_kp(const vp4_params *p) {
   k.inv_ms = 1.0 / k.ms;
   k.inv_mv = 1.0 / k.mv;
   k.cap = list_cap(p->ss, p->sv);
-  k.direct = k.ms <= 2 && k.E <= DIRECT_MAX;
+  k.direct = k.E <= DIRECT_FEW || (k.ms <= 2 && k.E <= DIRECT_MAX);
   k.L = p->L;
   k.hL = 0.5 * p->L;
   k.vmax = p->vmax;
@@ -203,7 +203,9 @@ int launch_elem(vp4_ctx *c, int kick, int drift, int predict, int reg_buf,
                 int zero_buf) {
   Prof ps(c, kick ? PK_KICK : PK_PREDICT);
   const bool clear = zero_buf >= 0 && !c->k.direct;
-  hipLaunchKernelGGL(k4_elem, dim3(grid_for(c->k.E, EPW)), dim3(256), 0,
+  const int epw = elem_epw(c->k.E);
+  auto kern = epw == 16 ? k4_elem<16> : epw == 4 ? k4_elem<4> : k4_elem<1>;
+  hipLaunchKernelGGL(kern, dim3(grid_for(c->k.E, epw)), dim3(256), 0,
                      c->stream, c->k, c->at<double>(c->L.st),
                      c->at<double>(c->L.fld), c->at<double>(c->L.rec),
                      clear ? c->counts(zero_buf) : nullptr,

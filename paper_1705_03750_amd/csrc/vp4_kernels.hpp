@@ -36,14 +36,14 @@ constexpr int RS = 64;                     // record doubles (512 bytes)
 constexpr int R_A = 4, R_K = 20, R_DELTA = 21, R_G = 24;  // record offsets
 constexpr int BLK = 4;                     // sites per axis of a block
 constexpr int SPAN = 4096;                 // max blocks of one element
-// Grids without lists: at most DIRECT_MAX elements, at most two per ring (a
-// window of the undeformed lattice then covers the ring already, so that lists
-// hold every element, most of them more than once, and one to four workgroups
-// make all the claims).  us for f with lists / without: 8^4, stride 4, 16
-// elements 46 / 31; 16^4, stride 8 61 / 28; 32^4, stride 16 354 / 92; 16^4,
-// strides 8 and 4, 64 elements 74 / 59.  Above: three per ring (24^2 x 8^2) 45 /
-// 41, but a step 66 with lists and 79 with the scan they replaced; 144 elements
-// (8^2 x 24^2) 77 / 109.
+// Grids without lists: at most DIRECT_FEW elements, or DIRECT_MAX where a ring
+// holds at most two (a window of the undeformed lattice then covers it already,
+// and lists hold every element, most of them more than once).  us for f with
+// lists / without: 8^4, stride 4, 16 elements 44 / 28; 16^4, stride 8 43 / 29;
+// 32^4, stride 16 106 / 88; 16^2 x 8^2, strides 4 and 8, sheared 39 / 28; 8^2 x
+// 16^2, stride 4, 64 elements, sheared 67 / 54.  Above: 36 elements, three per
+// ring (24^2 x 8^2) 32 / 41; 144 elements (8^2 x 24^2) 77 / 109.
+constexpr int DIRECT_FEW = 16;
 constexpr int DIRECT_MAX = 64;
 enum { FL_NUMERIC = 1, FL_WIDE = 2 };
 enum { M_DENSITY = 0, M_F = 1, M_ASSIGN = 2 };
@@ -232,13 +232,22 @@ __device__ __forceinline__ double tsc_field(const KP &p,
 // entry), then the (element, block) pairs of the registration.  One thread
 // per element kept 60 entries in registers and walked its 81 or more blocks
 // one after another, each with an atomic to wait for: 159 us at 64^4 (65536
-// elements) and 126 us at 16^4 (256), against 97 and 15 us on average for this
+// elements) and 126 us at 16^4 (256), against 97 and 11 us on average for this
 // pass, the kick (18 and 9 us as its own launch) included.  It waits on the
 // slot claims' device atomics.
-constexpr int EPW = 16;
-constexpr int EP1 = EPW + 1;  // LDS pitch
+//
+// EPW from the number of elements (elem_epw): 16 share the lines of the state
+// rows, but a workgroup's claims are a chain of rounds, up to 16 x 4096 pairs of
+// sheared elements on a narrow ring, so that a pass of few elements is spread
+// over more workgroups.  us per step with 16 / 4 / 1 (stride 4, sheared): 256
+// elements 24 / 13 / 11, 1024 25 / 16 / 15, 2304 29 / 20 / 27, 4096 30 / 23 / 34,
+// 6400 33 / 32 / 47, 9216 36 / 37 / 61, 65536 149 / 167 / 394; stride 8 on 32 and
+// 64 sites, 256 elements 93 / 34 / 15, 4096 133 / 75 / 70.
 constexpr int REG_AHEAD = 4;  // pairs in flight per thread
+inline int elem_epw(int E) { return E <= 1024 ? 1 : E <= 8192 ? 4 : 16; }
+template <int EPW>
 struct ElemLds {
+  static constexpr int EP1 = EPW + 1;  // pitch
   double s[NST][EP1], A[16][EP1], f[12][EP1], u[4][EP1];
   double k[EPW], delta[EPW];
   int blo[4][EP1], ext[4][EP1], at[EP1];
@@ -263,7 +272,8 @@ __device__ __forceinline__ void moving_row(int r, int &space, int &vel) {
 // block whose sites span [g0, g1] per axis (space columns unwrapped)?  l = A dP is
 // linear, so over the block's box each l_a ranges over its centre value +-
 // sum_b |A_ab| half-width_b; rounding margins as in the 2D engine.
-__device__ __forceinline__ bool block_meets(const KP &p, const ElemLds &S,
+template <int EPW>
+__device__ __forceinline__ bool block_meets(const KP &p, const ElemLds<EPW> &S,
                                             int e, const int g0[4],
                                             const int g1[4]) {
   double m[4], h[4];
@@ -289,12 +299,13 @@ __device__ __forceinline__ bool block_meets(const KP &p, const ElemLds &S,
   return true;
 }
 
+template <int EPW>
 __global__ __launch_bounds__(256) void k4_elem(
     KP p, double *__restrict__ st, const double *__restrict__ fld,
     double *__restrict__ rec, int *__restrict__ cnt_zero, long long nzero,
     int *__restrict__ cnt_reg, int *__restrict__ lst, int *__restrict__ flags,
     int kick, int drift, int predict) {
-  __shared__ ElemLds S;
+  __shared__ ElemLds<EPW> S;
   const int tid = threadIdx.x;
   const long long gsz = (long long)gridDim.x * 256;
   for (long long i = (long long)blockIdx.x * 256 + tid; i < nzero; i += gsz)
@@ -380,7 +391,7 @@ __global__ __launch_bounds__(256) void k4_elem(
     for (int a = 0; a < 4; ++a) bad = bad || !isfinite(S.s[S_P + a][tid]);
     if (tid < ne && bad) atomicOr(flags, FL_NUMERIC);
   }
-  if (tid < 64) {
+  if (tid < 4 * EPW) {
     // four threads per element, one per axis (wavefront 0)
     const int e = tid >> 2, a = tid & 3;
     bad = __shfl(bad, e);
