@@ -80,9 +80,12 @@ def test_claims_of_few_sheared_elements(orc):
     g.init_conditions(f / f.mean())
     g.step(30)
     g.reconstruct_f()
-    g.prof_begin(64)
-    for _ in range(8):
-        g.reconstruct_f()
-    ms = g.prof_end()
-    print({k: v for k, v in ms.items() if v[1]})
-    assert ms["predict"][0] <= ms["recon"][0], ms
+    ms = []  # the least of five: a launch may be held up by something else
+    for _ in range(5):
+        g.prof_begin(64)
+        for _ in range(8):
+            g.reconstruct_f()
+        r = g.prof_end()
+        ms.append((r["predict"][0], r["recon"][0]))
+    predict, recon = (min(t) for t in zip(*ms))
+    assert predict <= recon, ms

@@ -17,7 +17,7 @@ def pair(ns, nv, ss, sv, **kw):
     import paper_1705_03750_amd.vp4 as v4
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    print(f"[4d scan] ns={ns} nv={nv} ss={ss} sv={sv} {kw}", flush=True)
+    print(f"[4d few] ns={ns} nv={nv} ss={ss} sv={sv} {kw}", flush=True)
     p = dict(ns=ns, nv=nv, L=L, vmax=VMAX, ss=ss, sv=sv, G=-0.5, dt=0.1)
     o, g = o4.Oracle4(**p), v4.VlasovRun4(device="cuda:0", **p, **kw)
     f0 = np.random.default_rng(ns * 100 + nv).uniform(0.5, 1.0, o.shape)
@@ -66,8 +66,11 @@ def test_element_pass_without_lists(orc):
     for ns, s in ((8, 4), (32, 16)):
         _, g = pair(ns, ns, s, s)
         g.reconstruct_f()
-        g.prof_begin(64)
-        for _ in range(8):
-            g.reconstruct_f()
-        ms[ns] = g.prof_end()["predict"][0]
+        t = []  # the least of five: a launch may be held up by something else
+        for _ in range(5):
+            g.prof_begin(64)
+            for _ in range(8):
+                g.reconstruct_f()
+            t.append(g.prof_end()["predict"][0])
+        ms[ns] = min(t)
     assert ms[32] <= 3.0 * ms[8], ms
